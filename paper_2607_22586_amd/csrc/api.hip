@@ -22,7 +22,6 @@ double query_scale(int d) { return 1.4426950408889634074 / sqrt(static_cast<doub
 
 constexpr size_t kAlign = 256;
 constexpr size_t kMaxRowLds = 96 * 1024;   // Gh * P + 32 rows of fp32 in LDS
-constexpr size_t kMaxRowLds8 = 64 * 1024;  // the same with 8-wave mass blocks
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -87,27 +86,25 @@ int status_of(hipError_t e) { return e == hipSuccess ? MMSKV_OK : MMSKV_EHIP; }
 
 struct ScoreLayout {
     ScorePlan plan;
-    int n_kb, block_keys, mass_n_kb, rows, rows_pad;
+    int n_kb, block_keys, mass_n_kb, rows, rows_pad, mass_unit;
     size_t part_bytes, lse_off, total;
 };
 
 ScoreLayout score_layout(const mmskv_shape* s, const mmskv_params* p) {
     ScoreLayout l;
     const int Gh = s->Hq / s->Hkv;
-    l.plan = score_plan(s->B, s->Hkv, s->T);
+    l.rows = Gh * p->P;
+    l.rows_pad = l.rows + 32 * ((Gh + 31) / 32);
+    // pass 2 splits its rows between proxy groups: a group is g16 16-row
+    // halves, so a unit of whole 32-row proxy blocks is g16 blocks (two
+    // groups) when g16 is odd and g16 / 2 (one group) otherwise
+    const int g16 = p->P / p->G / 16;
+    l.mass_unit = g16 % 2 ? g16 : g16 / 2;
+    l.plan = score_plan(s->B, s->Hkv, s->T, l.rows_pad, Gh, p->P / 32 / l.mass_unit, l.mass_unit);
     const int lse_keys = 32 * l.plan.lse_sub * l.plan.lse_waves;
     l.n_kb = (s->T + lse_keys - 1) / lse_keys;
     l.block_keys = 64 * l.plan.mass_waves;
     l.mass_n_kb = (s->T + l.block_keys - 1) / l.block_keys;
-    l.rows = Gh * p->P;
-    l.rows_pad = l.rows + 32 * ((Gh + 31) / 32);
-    // 8-wave mass blocks hold 8 staged tiles (68 KiB at d = 128) next to the
-    // row normalisers; many rows take 4-wave blocks, which stage 4
-    if (l.plan.mass_waves == 8 && static_cast<size_t>(l.rows_pad) * sizeof(float) > kMaxRowLds8) {
-        l.plan.mass_waves = 4;
-        l.block_keys = 64 * l.plan.mass_waves;
-        l.mass_n_kb = (s->T + l.block_keys - 1) / l.block_keys;
-    }
     const size_t heads = static_cast<size_t>(s->B) * s->Hkv;
     l.part_bytes = heads * l.n_kb * l.rows_pad * sizeof(float2);
     l.lse_off = align_up(l.part_bytes);
@@ -170,11 +167,15 @@ int prepare_score(const mmskv_shape* shape, const mmskv_params* params, const ui
     a->n_kb = l.n_kb;
     a->block_keys = l.block_keys;
     a->mass_n_kb = l.mass_n_kb;
+    a->lse_parts = l.plan.lse_parts;
+    a->mass_parts = l.plan.mass_parts;
+    a->mass_unit = l.mass_unit;
     a->rows = l.rows;
     a->rows_pad = l.rows_pad;
     a->anchor_scale = query_scale(shape->d);
     a->lane_sum_hi = lane_sum_limit(shape->T, 16);     // pass 1 sums 16 keys per lane and chain
     a->part = static_cast<float2*>(ws);
+    a->mass_part = static_cast<float*>(ws);
     a->lse = reinterpret_cast<float*>(static_cast<char*>(ws) + l.lse_off);
     a->group_mass = nullptr;
     a->mass = nullptr;

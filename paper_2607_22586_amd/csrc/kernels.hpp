@@ -8,11 +8,17 @@
 namespace mmskv {
 
 // Workgroup shapes of the two score passes for a problem size: pass 1 runs
-// lse_waves waves of 32 * lse_sub keys each, pass 2 mass_waves waves of 64.
+// lse_waves waves of 32 * lse_sub keys each, pass 2 mass_waves waves of 64;
+// lse_parts and mass_parts workgroups share each key block's rows (rows_pad
+// rows in pass 1; in pass 2 mass_units units of mass_unit proxy blocks, one
+// 32-row tile of each of the Gh heads per proxy block).
+constexpr int kMaxMassParts = 16;
+constexpr size_t kMaxRowLds8 = 64 * 1024;  // row normalisers (fp32) in LDS with 8-wave mass blocks
+constexpr int kPlanCus = 256;              // CUs of the chip
 struct ScorePlan {
-    int lse_waves, lse_sub, mass_waves;
+    int lse_waves, lse_sub, mass_waves, lse_parts, mass_parts;
 };
-ScorePlan score_plan(int B, int Hkv, int T);
+ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units, int mass_unit);
 
 struct ProxyArgs {
     const void* q;        // [B, Hq, W, d]
@@ -40,6 +46,8 @@ struct ScoreArgs {
     int n_kb;                  // pass-1 key blocks (32 * lse_sub * lse_waves keys each)
     int block_keys;            // pass 2: keys per workgroup (64 * waves)
     int mass_n_kb;             // pass-2 key blocks
+    int lse_parts, mass_parts; // workgroups that share a key block's rows
+    int mass_unit;             // pass 2: proxy blocks (32 proxies of each head) per split unit
     int rows;                  // Gh * P proxy rows per KV head
     int rows_pad;              // rows + 32 * ceil(Gh / 32) (anchor rows, padded)
     double anchor_scale;       // log2(e) / sqrt(d), applied to the anchor rows as they are staged
@@ -48,6 +56,7 @@ struct ScoreArgs {
     float* lse;                // [B, Hkv, rows_pad]        log2-domain
     float* group_mass;         // [B, Hkv, G, T] or null
     float* mass;               // [B, Hkv, T]
+    float* mass_part;          // [mass_parts, B, Hkv, T] when mass_parts > 1 (in part's memory, which pass 2 does not read)
     float* anchor;             // [B, Hkv, T]
 };
 

@@ -27,6 +27,13 @@
 //               into the total mass, and over the anchor rows.  Each key
 //               column belongs to one wave, so there are no atomics and the
 //               result is deterministic.
+// Where the key blocks alone leave CUs idle (short prompts, few heads, or a
+// last round of workgroups that is nearly empty), several workgroups share a
+// key block, each taking a part of its rows: pass 1 splits by tiles (every
+// row's sums stay in one workgroup), pass 2 by proxy groups (every group mass
+// stays in one workgroup; the total masses of the parts are added in part
+// order by mass_combine).  score_plan picks block sizes and parts.
+//
 // The query rows carry the softmax scale log2(e)/sqrt(d) (the proxies from
 // their construction, the anchor rows from their staging here, both in fp64
 // before the bf16 rounding), so s = q~ . k is a base-2 logit and
@@ -71,14 +78,23 @@ __device__ __forceinline__ floatx16 zero16() {
     return z;
 }
 
-// Block -> (head, key block), grouping each head's key blocks on one XCD.
-__device__ __forceinline__ void block_work(int n_kb, int& head, int& kb) {
+// Block -> (head, key block, row part), grouping each head's blocks on one
+// XCD; the parts of a key block are neighbours, so its keys come from memory
+// once and from that L2 for the other parts.
+__device__ __forceinline__ void block_work(int n_kb, int parts, int& head, int& kb, int& part) {
     const int n = static_cast<int>(gridDim.x);
     const int id = static_cast<int>(blockIdx.x);
     const int q = n / 8, r = n % 8, x = id % 8;
     const int logical = x * q + min(x, r) + id / 8;
-    head = logical / n_kb;
-    kb = logical - head * n_kb;
+    const int kp = logical / parts;
+    part = logical - kp * parts;
+    head = kp / n_kb;
+    kb = kp - head * n_kb;
+}
+
+// First of the n units (tiles, or proxy blocks) of row part `part` of `parts`.
+__device__ __forceinline__ int part_begin(int n, int part, int parts) {
+    return static_cast<int>(static_cast<int64_t>(n) * part / parts);
 }
 
 // A 32-row tile of bf16 rows of D elements in LDS, each row padded by one
@@ -271,8 +287,9 @@ constexpr int kEarlySubs = 4;     // sub-tiles per wave of that schedule
 // (max, sum) pair is merged by the max-and-rescale rule.  Per tile, the two half-waves' sums of each
 // column are combined and the waves' pairs are merged every kMergeTiles tiles
 // into one partial per (row, key block).  FULL: every key of the block is < T.
+// The block takes tiles [tile0, tile0 + n_tiles) of the row space.
 template <int D, int WAVES, int NS, bool FULL, bool EARLY, int SLOTS>
-__device__ __forceinline__ void lse_body(const ScoreArgs& a, int head, int kb, int b, int c,
+__device__ __forceinline__ void lse_body(const ScoreArgs& a, int head, int kb, int b, int c, int tile0, int n_tiles,
                                          u32x4 (&stage)[SLOTS][TileLds<D>::kSlots],
                                          float2 (&mrg)[2][kMergeTiles][WAVES][32]) {
     using St = Stager<D, WAVES>;
@@ -280,31 +297,61 @@ __device__ __forceinline__ void lse_body(const ScoreArgs& a, int head, int kb, i
     static_assert(NS % 2 == 0, "chains alternate between two accumulator sets");
     static_assert(!EARLY || (FULL && NS == kEarlySubs && SLOTS >= kEarlyTiles && kEarlyTiles >= kRing),
                   "the early tiles are full blocks of four sub-tiles in their own LDS slots");
-    const int wave = static_cast<int>(threadIdx.x) / kWave, lane = lane_id();
+    // (scalar: the branches on a ragged block's sub-tiles are scalar branches)
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave), lane = lane_id();
     const int key0 = kb * (32 * NS * WAVES) + wave * (32 * NS);
 
-    bf16x8 kf[NS][KC];
-    if constexpr (!EARLY) load_keys<D, NS>(a, b, c, key0, kf);
-    // keys of sub-tile s held by this lane that are < T: value i is key
-    // key0 + 32 s + 8 (i / 4) + 4 (lane / 32) + i % 4, valid while
-    // 8 (i / 4) + i % 4 < n_keys(s)
-    auto n_keys = [&](int s2) { return a.T - key0 - 32 * s2 - 4 * (lane >> 5); };
+    // In a ragged block, a wave holds n_full sub-tiles of keys < T and at
+    // most one that straddles T.  That one goes to slot NS - 1, whose chain
+    // starts from `start` (0 for a key < T, -inf past T, so that its 2^s is
+    // 0) instead of zero; the slots in between hold no keys and their chains
+    // are left out of the sums.  No chain thus has an instruction or branch
+    // more than in a full block (with the mask formed anew in each chain, a
+    // ragged block took 94 us where a full one takes 66).
+    const int n_full = FULL ? NS : min(max((a.T - key0) / 32, 0), NS);
+    const int last = min(n_full, NS - 1);       // sub-tile in slot NS - 1
+    auto slot_empty = [&](int s2) { return !FULL && s2 < NS - 1 && s2 >= n_full; };
+    // keys of slot NS - 1 held by this lane that are < T: value i is key
+    // key0 + 32 last + 8 (i / 4) + 4 (lane / 32) + i % 4, valid while
+    // 8 (i / 4) + i % 4 < nk
+    const int nk = a.T - key0 - 32 * last - 4 * (lane >> 5);
+    // The start is held in 16 registers, or, beside four sub-tiles of keys at
+    // d = 128 (which leave none), formed by one MFMA of outer product form
+    // from a register that holds the start of row lane % 32 (k = 0; 0 at
+    // k = 1, the upper lanes) and a register of ones.
+    constexpr bool kStartMfma = !FULL && NS * D >= 512;
+    floatx16 start = zero16();
+    float row_start = 0.f, ones = 1.f;
+    if constexpr (kStartMfma) {
+        row_start = (lane >= 32 || (lane & 31) < a.T - key0 - 32 * last) ? 0.f : -INFINITY;
+        asm volatile("" : "+v"(ones));
+    } else if constexpr (!FULL) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) start[i] = (8 * (i >> 2) + (i & 3) < nk) ? 0.f : -INFINITY;
+    }
 
-    const int n_tiles = a.rows_pad / 32;
-    const int n_prox = a.rows / 32;
+    bf16x8 kf[NS][KC];
+    if constexpr (FULL && !EARLY) {
+        load_keys<D, NS>(a, b, c, key0, kf);
+    } else if constexpr (!FULL) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) load_key_sub<D>(a, b, c, slot_empty(s) ? a.T : key0, s < NS - 1 ? s : last, kf[s]);
+    }
+
+    const int n_prox = min(max(a.rows / 32 - tile0, 0), n_tiles);     // local tiles of proxy rows
     const int64_t hq0 = static_cast<int64_t>(b) * a.Hq + static_cast<int64_t>(c) * a.Gh;
-    const uint16_t* pbase = a.proxies + hq0 * a.P * D;
+    const uint16_t* pbase = a.proxies + (hq0 * a.P + 32 * tile0) * D;
     int off[St::kPer];
 #pragma unroll
     for (int k = 0; k < St::kPer; ++k) off[k] = St::src_off(k);
     St st;
-    // tile t = rows [32t, 32t+32) of the padded row space
+    // tile t = rows [32 (tile0 + t), +32) of the padded row space
     auto load_tile = [&](int t) {
         if (t < n_prox) st.load_block(pbase + static_cast<int64_t>(32 * t) * D, off);
-        else st.load_anchor(a, hq0, t - n_prox);
+        else st.load_anchor(a, hq0, tile0 + t - a.rows / 32);
     };
 
-    float2* part = a.part + (static_cast<int64_t>(head) * a.n_kb + kb) * a.rows_pad;
+    float2* part = a.part + (static_cast<int64_t>(head) * a.n_kb + kb) * a.rows_pad + 32 * tile0;
     // merged (max, sum) over the waves of tiles [16k, 16k+16), all threads
     auto merge_chunk = [&](int k) {
         const int n_in = min(kMergeTiles, n_tiles - kMergeTiles * k);
@@ -352,10 +399,11 @@ __device__ __forceinline__ void lse_body(const ScoreArgs& a, int head, int kb, i
     // needed, the exact form
     auto finish_chain = [&](auto setp, auto sp, float nsf) {
         constexpr int SETP = decltype(setp)::value, SP = decltype(sp)::value;
-        // a lane whose keys are all past T has nothing to sum
-        const bool in_range = (nsf >= 0x1p-60f || (!FULL && n_keys(SP) <= 0)) && nsf < a.lane_sum_hi;
+        // a slot without keys, or a lane whose keys are all past T, has nothing to sum
+        const bool skip = slot_empty(SP);
+        const bool in_range = skip || ((nsf >= 0x1p-60f || (!FULL && SP == NS - 1 && nk <= 0)) && nsf < a.lane_sum_hi);
         if (__ballot(!in_range) == 0) {
-            sf = nsf;
+            sf = !skip ? nsf : SP == 0 ? 0.f : sf;
         } else {
             // the tile's first chain starts the running sum
             if (SP == 0) sf = 0.f;
@@ -439,18 +487,17 @@ __device__ __forceinline__ void lse_body(const ScoreArgs& a, int head, int kb, i
             // tile's first chain, SP == 0, starts it from -0, the additive
             // identity, so that first add is no instruction)
             float l0 = SP == 0 ? -0.f : sf, l1 = -0.f;
-            if (!FULL && MF) {
-                // keys past T start at -inf, so their 2^s is 0 (the mask is
-                // opaque here so that the start values are not kept live
-                // across the loop)
-                int nk = n_keys(S);
-                asm volatile("" : "+v"(nk));
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[CUR][i] = (8 * (i >> 2) + (i & 3) < nk) ? 0.f : -INFINITY;
-            }
 #pragma unroll
             for (int kc = 0; kc < KC; ++kc) {
-                if (MF) acc[CUR] = mfma32(kf[S][kc], A[AS][kc], kc == 0 ? (FULL ? zero16() : acc[CUR]) : acc[CUR]);
+                if (MF && kc == 0) {
+                    if (kStartMfma && S == NS - 1 && n_full < NS)
+                        acc[CUR] = mfma32(kf[S][0], A[AS][0],
+                                          __builtin_amdgcn_mfma_f32_32x32x2f32(row_start, ones, zero16(), 0, 0, 0));
+                    else
+                        acc[CUR] = mfma32(kf[S][0], A[AS][0], !FULL && !kStartMfma && S == NS - 1 ? start : zero16());
+                } else if (MF) {
+                    acc[CUR] = mfma32(kf[S][kc], A[AS][kc], acc[CUR]);
+                }
                 __builtin_amdgcn_sched_barrier(0);
                 // the previous chain's values go to slots 1 .. KC-1, so none of
                 // them is read before its last MFMA has had a slot to finish
@@ -658,21 +705,23 @@ __global__ void __launch_bounds__(64 * WAVES) score_lse_kernel(ScoreArgs a) {
     constexpr int kSlotsAll = kEarly ? kEarlyTiles : kRing;
     __shared__ u32x4 stage[kSlotsAll][TileLds<D>::kSlots];
     __shared__ float2 mrg[2][kMergeTiles][WAVES][32];
-    int head, kb;
-    block_work(a.n_kb, head, kb);
+    int head, kb, part;
+    block_work(a.n_kb, a.lse_parts, head, kb, part);
     const int b = head / a.Hkv, c = head - b * a.Hkv;
+    const int tile0 = part_begin(a.rows_pad / 32, part, a.lse_parts);
+    const int n_tiles = part_begin(a.rows_pad / 32, part + 1, a.lse_parts) - tile0;
     if ((kb + 1) * (32 * NS * WAVES) <= a.T) {
         // the early schedule needs every tile it stages ahead to be a proxy
         // tile, and bf16 keys (loaded without conversion)
         if constexpr (kEarly) {
-            if (a.rows / 32 >= 2 * kMergeTiles && a.k_dtype == 1) {
-                lse_body<D, WAVES, NS, true, true>(a, head, kb, b, c, stage, mrg);
+            if (min(tile0 + n_tiles, a.rows / 32) - tile0 >= 2 * kEarlyTiles && a.k_dtype == 1) {
+                lse_body<D, WAVES, NS, true, true>(a, head, kb, b, c, tile0, n_tiles, stage, mrg);
                 return;
             }
         }
-        lse_body<D, WAVES, NS, true, false>(a, head, kb, b, c, stage, mrg);
+        lse_body<D, WAVES, NS, true, false>(a, head, kb, b, c, tile0, n_tiles, stage, mrg);
     } else {
-        lse_body<D, WAVES, NS, false, false>(a, head, kb, b, c, stage, mrg);
+        lse_body<D, WAVES, NS, false, false>(a, head, kb, b, c, tile0, n_tiles, stage, mrg);
     }
 }
 
@@ -724,7 +773,7 @@ struct TileCursor {
 // of a tile is one group) and 5 to 8 query heads per KV head (tiles 0-7 then
 // close exactly one proxy block); see the early phase below.
 template <int D, int WAVES, bool EARLY, int SLOTS>
-__device__ __forceinline__ void mass_body(const ScoreArgs& a, int head, int kb,
+__device__ __forceinline__ void mass_body(const ScoreArgs& a, int head, int kb, int part,
                                           u32x4 (&stage)[SLOTS][TileLds<D>::kSlots], float* Llds) {
     using St = Stager<D, WAVES>;
     static_assert(!EARLY || SLOTS >= kEarlyTiles, "the early tiles have their own LDS slots");
@@ -739,16 +788,21 @@ __device__ __forceinline__ void mass_body(const ScoreArgs& a, int head, int kb,
     if constexpr (!EARLY) load_keys<D>(a, b, c, key0, kf);
 
     const int g16 = a.P / a.G / 16;          // 16-row halves per proxy group
-    const int n_prox = (a.P / 32) * a.Gh;
-    const int n_anc = (a.rows_pad - a.rows) / 32;
+    // this block's proxy blocks (32 proxies of each head): u0 .. u0 + n_u, a
+    // whole number of groups; the last part also takes the anchor tiles
+    const int units = a.P / 32 / a.mass_unit;
+    const int u0 = part_begin(units, part, a.mass_parts) * a.mass_unit;
+    const int n_u = part_begin(units, part + 1, a.mass_parts) * a.mass_unit - u0;
+    const int n_prox = n_u * a.Gh;
+    const int n_anc = part == a.mass_parts - 1 ? (a.rows_pad - a.rows) / 32 : 0;
     const int64_t hq0 = static_cast<int64_t>(b) * a.Hq + static_cast<int64_t>(c) * a.Gh;
     const uint16_t* pbase = a.proxies + hq0 * a.P * D;
     int off[St::kPer];
 #pragma unroll
     for (int k = 0; k < St::kPer; ++k) off[k] = St::src_off(k);
 
-    // proxy tile (u, h): rows 32u.. of head h, first row h*P + 32u
-    auto tile_row = [&](const TileCursor& q) { return q.h * a.P + 32 * q.u; };
+    // proxy tile (u, h): rows 32 (u0 + u).. of head h, first row h*P + 32 (u0 + u)
+    auto tile_row = [&](const TileCursor& q) { return q.h * a.P + 32 * (u0 + q.u); };
     auto load_tile = [&](St& st, const TileCursor& q) {
         st.load_block(pbase + static_cast<int64_t>(tile_row(q)) * D, off);
     };
@@ -817,7 +871,7 @@ __device__ __forceinline__ void mass_body(const ScoreArgs& a, int head, int kb,
     const bool my_ok = my_key < a.T;
     float runA[kSub][2] = {}, runB[kSub][2] = {}, open[kSub] = {0.f, 0.f};
     float macc = 0.f;
-    int g_half = 0, g_idx = 0;               // halves in the open group, its index
+    int g_half = 0, g_idx = 2 * u0 / g16;    // halves in the open group, its index
     auto close_half = [&](float (&run)[kSub][2]) {
 #pragma unroll
         for (int s = 0; s < kSub; ++s) {
@@ -1028,9 +1082,9 @@ __device__ __forceinline__ void mass_body(const ScoreArgs& a, int head, int kb,
         for (int h2 = 0; h2 < 2; ++h2) {
             const float tot = pair_sum(fold[h2][0], fold[h2][1]);
             macc += tot;
-            if (a.group_mass != nullptr) a.group_mass[gm_base + static_cast<int64_t>(h2) * a.T + my_key] = tot;
+            if (a.group_mass != nullptr) a.group_mass[gm_base + static_cast<int64_t>(g_idx + h2) * a.T + my_key] = tot;
         }
-        g_idx = 2;
+        g_idx += 2;
         gs_h = kEarlyTiles % a.Gh;           // heads of proxy block 1 already summed
         // the anchor tile (Gh <= 8 rows: one tile) goes to early slot 4,
         // which nothing writes again, so the pipeline's end reads it there
@@ -1104,8 +1158,10 @@ __device__ __forceinline__ void mass_body(const ScoreArgs& a, int head, int kb,
     const float anc = pair_sum(aacc[0], aacc[1]) * (1.0f / static_cast<float>(a.Gh));
     if (my_ok) {
         const int64_t o = static_cast<int64_t>(head) * a.T + my_key;
-        a.mass[o] = macc;
-        a.anchor[o] = anc;
+        // with several parts, each writes its own row of partial masses
+        if (a.mass_parts == 1) a.mass[o] = macc;
+        else a.mass_part[static_cast<int64_t>(part) * a.B * a.Hkv * a.T + o] = macc;
+        if (n_anc > 0) a.anchor[o] = anc;
     }
 }
 
@@ -1115,24 +1171,39 @@ __global__ void __launch_bounds__(64 * WAVES) score_mass_kernel(ScoreArgs a) {
     __shared__ u32x4 stage[kEarly ? kEarlyTiles : kRing][TileLds<D>::kSlots];
     extern __shared__ float4 dyn_lds[];
     float* Llds = reinterpret_cast<float*>(dyn_lds);     // [rows_pad]
-    int head, kb;
-    block_work(a.mass_n_kb, head, kb);
+    int head, kb, part;
+    block_work(a.mass_n_kb, a.mass_parts, head, kb, part);
     if constexpr (kEarly) {
         // (the early phase and the pipeline's start load tiles 0 .. 12 as
         // proxy tiles, so a head must have at least 16 of them)
         if ((kb + 1) * 64 * WAVES <= a.T && a.k_dtype == 1 && a.P == 16 * a.G && a.Gh >= 5 &&
-            a.Gh <= kEarlyTiles && (a.P / 32) * a.Gh >= 2 * kEarlyTiles) {
-            mass_body<D, WAVES, true>(a, head, kb, stage, Llds);
+            a.Gh <= kEarlyTiles && (a.P / 32 / a.mass_parts) * a.Gh >= 2 * kEarlyTiles) {
+            mass_body<D, WAVES, true>(a, head, kb, part, stage, Llds);
             return;
         }
     }
-    mass_body<D, WAVES, false>(a, head, kb, stage, Llds);
+    mass_body<D, WAVES, false>(a, head, kb, part, stage, Llds);
+}
+
+// Total mass of every key from the row parts' partial masses, in part order.
+__global__ void __launch_bounds__(256) mass_combine_kernel(ScoreArgs a) {
+    const int64_t n = static_cast<int64_t>(a.B) * a.Hkv * a.T;
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n) return;
+    float v[kMaxMassParts];
+#pragma unroll
+    for (int p = 0; p < kMaxMassParts; ++p) v[p] = p < a.mass_parts ? a.mass_part[p * n + i] : 0.f;
+    float m = v[0];
+#pragma unroll
+    for (int p = 1; p < kMaxMassParts; ++p) m += v[p];
+    a.mass[i] = m;
 }
 
 template <int D, int WAVES, int NS>
 hipError_t lse_impl(const ScoreArgs& a, int stages, hipStream_t s) {
     if (stages & kLseBlocks) {
-        hipLaunchKernelGGL((score_lse_kernel<D, WAVES, NS>), dim3(a.B * a.Hkv * a.n_kb), dim3(64 * WAVES), 0, s, a);
+        hipLaunchKernelGGL((score_lse_kernel<D, WAVES, NS>), dim3(a.B * a.Hkv * a.n_kb * a.lse_parts),
+                           dim3(64 * WAVES), 0, s, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1146,8 +1217,12 @@ hipError_t lse_impl(const ScoreArgs& a, int stages, hipStream_t s) {
 
 template <int D, int WAVES>
 hipError_t mass_impl(const ScoreArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((score_mass_kernel<D, WAVES>), dim3(a.B * a.Hkv * a.mass_n_kb), dim3(64 * WAVES),
+    hipLaunchKernelGGL((score_mass_kernel<D, WAVES>), dim3(a.B * a.Hkv * a.mass_n_kb * a.mass_parts), dim3(64 * WAVES),
                        static_cast<size_t>(a.rows_pad) * sizeof(float), s, a);
+    if (a.mass_parts > 1) {
+        const int64_t n = static_cast<int64_t>(a.B) * a.Hkv * a.T;
+        hipLaunchKernelGGL(mass_combine_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, a);
+    }
     return hipGetLastError();
 }
 
@@ -1161,35 +1236,87 @@ float lane_sum_limit(int T, int keys_per_sum) {
     return ldexpf(1.0f, e);
 }
 
-ScorePlan score_plan(int B, int Hkv, int T) {
-    // the largest key blocks that still give every CU one block of work:
-    // pass 1 with 8 waves of 128 keys, else 8 waves of 64, else 4 waves of
-    // 64; pass 2 with 8-wave blocks (512 keys) when that gives every CU two
-    // blocks, else 4-wave blocks (256 keys)
+namespace {
+
+// Modelled time (us) of n workgroups of `tiles` row tiles each.  A CU holds
+// one 8-wave workgroup or two 4-wave ones; a 4-wave workgroup alone on its CU
+// is faster than two that share it.
+struct BlockCost {
+    double start, tile;          // 8-wave workgroup, or two 4-wave ones on a CU
+    double tile_alone;           // 4-wave workgroup alone on its CU (0: 8-wave)
+};
+double plan_time(const BlockCost& c, long n, int tiles) {
+    const long slots = c.tile_alone > 0.0 ? 2 * kPlanCus : kPlanCus;
+    const long full = n / slots, rest = n % slots;
+    const double round = c.start + c.tile * tiles;
+    double t = full * round;
+    if (rest > 0) t += (c.tile_alone > 0.0 && rest <= kPlanCus) ? c.start + c.tile_alone * tiles : round;
+    return t;
+}
+
+// Measured at d = 128 (launches of 100 to 2000 workgroups, 4 to 113 tiles
+// each): a tile of 8-wave blocks of 128 keys per wave (pass 1) takes 1.72 us,
+// of two 4-wave blocks of 64 per wave 0.93 us, of one alone 0.58 us; the
+// start (launch, first tiles, keys) 7 to 9 us.  Pass 2 alike.
+constexpr BlockCost kLse8{9.0, 1.72, 0.0}, kLse4{7.0, 0.93, 0.58};
+constexpr BlockCost kMass8{5.5, 0.88, 0.0}, kMass4{5.5, 0.93, 0.53};
+constexpr double kMassCombine = 3.0;                 // mass_combine_kernel
+constexpr int kMaxLseParts = 16;
+
+}  // namespace
+
+// Block sizes and row parts with the smallest modelled time.  Large problems
+// (every CU has a whole 8-wave block of keys) keep all rows in one workgroup;
+// below that, and where the last round of workgroups would leave most CUs
+// idle, several workgroups share a key block's rows.  One layer of 28 query
+// and 4 KV heads, P = 512, both passes with all rows in one workgroup and
+// with the parts chosen here: T = 1000 157 -> 31 us, 4096 131 -> 50, 8191
+// 166 -> 77, 20000 238 -> 153; at 4 x 16384 keys more parts cost 7% each
+// doubling, since every part fetches the keys again.
+ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units, int mass_unit) {
     const long heads = static_cast<long>(B) * Hkv;
-    ScorePlan p;
-    if (heads * ((T + 1023) / 1024) >= 256) {
-        p.lse_waves = 8;
-        p.lse_sub = 4;
-    } else if (heads * ((T + 511) / 512) >= 256) {
-        p.lse_waves = 8;
-        p.lse_sub = 2;
-    } else {
-        p.lse_waves = 4;
-        p.lse_sub = 2;
+    const int tiles = rows_pad / 32;
+    ScorePlan p{};
+    double best = 0.0;
+    for (int w = 8; w >= 4; w -= 4) {
+        const int keys = w == 8 ? 1024 : 256;
+        const long n = heads * ((T + keys - 1) / keys);
+        for (int r = 1; r <= kMaxLseParts && (r == 1 || tiles / r >= 4); ++r) {
+            const double t = plan_time(w == 8 ? kLse8 : kLse4, n * r, (tiles + r - 1) / r);
+            if (p.lse_waves == 0 || t < best) {
+                best = t;
+                p.lse_waves = w;
+                p.lse_sub = keys / w / 32;
+                p.lse_parts = r;
+            }
+        }
     }
-    p.mass_waves = heads * ((T + 511) / 512) >= 512 ? 8 : 4;
+    // the partial masses of pass 2's row parts take the place of pass 1's
+    // partials, which are merged by then: no more parts than fit there
+    const int lse_keys = 32 * p.lse_sub * p.lse_waves;
+    const long fit = static_cast<long>((T + lse_keys - 1) / lse_keys) * rows_pad * 2 / T;
+    for (int w = 8; w >= 4; w -= 4) {
+        // 8-wave mass blocks hold 8 staged tiles (68 KiB at d = 128) next to
+        // the row normalisers; many rows take 4-wave blocks, which stage 4
+        if (w == 8 && static_cast<size_t>(rows_pad) * sizeof(float) > kMaxRowLds8) continue;
+        const long n = heads * ((T + 64 * w - 1) / (64 * w));
+        for (int r = 1; r <= kMaxMassParts && r <= mass_units && (r == 1 || r <= fit); ++r) {
+            const int part_tiles = (mass_units + r - 1) / r * mass_unit * Gh;
+            if (r > 1 && part_tiles < 4) break;
+            const double t = plan_time(w == 8 ? kMass8 : kMass4, n * r, part_tiles) + (r > 1 ? kMassCombine : 0.0);
+            if (p.mass_waves == 0 || t < best) {
+                best = t;
+                p.mass_waves = w;
+                p.mass_parts = r;
+            }
+        }
+    }
     return p;
 }
 
 hipError_t launch_score_lse(const ScoreArgs& a, int stages, hipStream_t s) {
-    const int w = a.lse_waves, ns = a.lse_sub;
-    if (a.d == 64) {
-        if (w == 8) return ns == 4 ? lse_impl<64, 8, 4>(a, stages, s) : lse_impl<64, 8, 2>(a, stages, s);
-        return lse_impl<64, 4, 2>(a, stages, s);
-    }
-    if (w == 8) return ns == 4 ? lse_impl<128, 8, 4>(a, stages, s) : lse_impl<128, 8, 2>(a, stages, s);
-    return lse_impl<128, 4, 2>(a, stages, s);
+    if (a.d == 64) return a.lse_waves == 8 ? lse_impl<64, 8, 4>(a, stages, s) : lse_impl<64, 4, 2>(a, stages, s);
+    return a.lse_waves == 8 ? lse_impl<128, 8, 4>(a, stages, s) : lse_impl<128, 4, 2>(a, stages, s);
 }
 
 hipError_t launch_score_mass(const ScoreArgs& a, hipStream_t s) {
