@@ -113,7 +113,7 @@ ScoreLayout score_layout(const mmskv_shape* s, const mmskv_params* p) {
 }
 
 struct SelectLayout {
-    size_t theta_off, tcut_off, keys_off, planes_off, hist_off, total;
+    size_t theta_off, tcut_off, keys_off, digits_off, planes_off, hist_off, total;
 };
 
 SelectLayout select_layout(const mmskv_shape* s, const mmskv_params* p) {
@@ -122,7 +122,8 @@ SelectLayout select_layout(const mmskv_shape* s, const mmskv_params* p) {
     l.theta_off = 0;
     l.tcut_off = align_up(heads * p->G * sizeof(uint32_t));
     l.keys_off = l.tcut_off + align_up(heads * p->G * sizeof(int32_t));
-    l.planes_off = l.keys_off + align_up(heads * static_cast<size_t>(select_key_stride(s->T)) * sizeof(uint64_t));
+    l.digits_off = l.keys_off + align_up(heads * static_cast<size_t>(s->T) * sizeof(uint64_t));
+    l.planes_off = l.digits_off + align_up(heads * static_cast<size_t>(select_digit_stride(s->T)) * sizeof(uint16_t));
     const size_t words = (static_cast<size_t>(s->T) + 31) / 32;
     l.hist_off = l.planes_off + align_up(heads * words * p->G * sizeof(uint32_t));
     l.total = l.hist_off + align_up(heads * 2048 * sizeof(uint32_t));
@@ -437,6 +438,11 @@ int select_call(const mmskv_shape* shape, const mmskv_params* params, const floa
     a.c_max = c_max;
     a.tau = params->tau;
     a.lambda = params->lambda;
+    // 2048 first digits over G + 1 vote counts; each vote's cover about 14
+    // octaves of the fraction (anchors of 1 down to 2^-14)
+    a.digit_sub = 2048 / (params->G + 1);
+    a.digit_q = 0;
+    while ((14 << (a.digit_q + 1)) <= a.digit_sub && a.digit_q < 6) ++a.digit_q;
     // fixed-point unit 2^-S with S = 62 - bitlen(rows per group), so a
     // group's total (<= rows per group, plus rounding) stays below 2^63
     {
@@ -451,8 +457,9 @@ int select_call(const mmskv_shape* shape, const mmskv_params* params, const floa
     a.keys = reinterpret_cast<uint64_t*>(w + l.keys_off);
     a.planes = reinterpret_cast<uint32_t*>(w + l.planes_off);
     a.hist0 = reinterpret_cast<uint32_t*>(w + l.hist_off);
+    a.digits = reinterpret_cast<uint16_t*>(w + l.digits_off);
     a.kpt = select_kpt(shape->T);
-    a.key_stride = select_key_stride(shape->T);
+    a.digit_stride = select_digit_stride(shape->T);
     a.idx = idx;
     a.counts = counts;
     a.votes = votes;

@@ -85,4 +85,17 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
+// Bitwise OR over the 64 lanes, the same in every lane.
+__device__ __forceinline__ uint64_t wave_or_u64(uint64_t x) {
+    x |= dpp_take<0x111, 0xF>(x);
+    x |= dpp_take<0x112, 0xF>(x);
+    x |= dpp_take<0x114, 0xF>(x);
+    x |= dpp_take<0x118, 0xF>(x);
+    x |= dpp_take<0x142, 0xA>(x);
+    x |= dpp_take<0x143, 0xC>(x);
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(x)), 63));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(x >> 32)), 63));
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+
 }  // namespace mmskv

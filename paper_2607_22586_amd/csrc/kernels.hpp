@@ -72,9 +72,11 @@ struct SelectArgs {
     int32_t* tcut;             // [B, Hkv, G] last admitted index among equals
     uint64_t* keys;            // [B, Hkv, T] score bits (fp64, non-negative)
     uint32_t* planes;          // [B, Hkv, G, ceil(T/32)] tau-set membership, bit j of word (g, w): key 32w+j in S_g
-    uint32_t* hist0;           // [B, Hkv, 2048] pool keys per top digit (bits 63..53) of the score key
-    int kpt;                   // keys per top-k thread (register path), 0 for the sweep path
-    int key_stride;            // per-head stride of `keys`: kpt * 1024 (key t at (t % kpt) * 1024 + t / kpt), else T
+    int digit_sub, digit_q;    // VOTE: first digits per vote, and log2 of the digits per octave of its fraction
+    uint32_t* hist0;           // [B, Hkv, 2048] pool keys per first digit of the score
+    uint16_t* digits;          // [B, Hkv, digit_stride] first digit of each key's score, plus 1
+    int kpt;                   // keys per top-k thread
+    int64_t digit_stride;      // kpt * 1024
     int32_t* idx;              // [B, Hkv, c_max]
     int32_t* counts;           // [B, Hkv]
     uint8_t* votes;            // [B, Hkv, T] or null
@@ -169,13 +171,10 @@ hipError_t launch_score_mass(const ScoreArgs& a, hipStream_t s);
 // first-digit counts (MASS); votes, scores and first-digit counts; top-k.
 constexpr int kSelectTau = 1, kSelectVote = 2, kSelectPick = 4;
 hipError_t launch_select(const SelectArgs& a, int stages, hipStream_t s);
-// Keys per thread of the register-resident top-k for T keys (0: the sweep
-// kernel), and the per-head stride of the score keys it implies.
+// Keys per thread of the top-k for T keys, and the per-head stride of the
+// first digits it implies.
 int select_kpt(int T);
-inline int select_key_stride(int T) {
-    const int k = select_kpt(T);
-    return k > 0 ? k * 1024 : T;
-}
+inline int64_t select_digit_stride(int T) { return static_cast<int64_t>(select_kpt(T)) * 1024; }
 hipError_t launch_gather(const GatherArgs& a, hipStream_t s);
 hipError_t launch_hidden_stats(const HiddenArgs& a, hipStream_t s);
 hipError_t launch_hidden_proxies(const HiddenArgs& a, hipStream_t s);

@@ -1281,7 +1281,8 @@ ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units
     for (int w = 8; w >= 4; w -= 4) {
         const int keys = w == 8 ? 1024 : 256;
         const long n = heads * ((T + keys - 1) / keys);
-        for (int r = 1; r <= kMaxLseParts && (r == 1 || tiles / r >= 4); ++r) {
+        // (with 4 rounds of workgroups, more parts no longer level the last)
+        for (int r = 1; r <= kMaxLseParts && (r == 1 || (tiles / r >= 4 && n * (r - 1) < 8 * kPlanCus)); ++r) {
             const double t = plan_time(w == 8 ? kLse8 : kLse4, n * r, (tiles + r - 1) / r);
             if (p.lse_waves == 0 || t < best) {
                 best = t;
@@ -1300,7 +1301,7 @@ ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units
         // the row normalisers; many rows take 4-wave blocks, which stage 4
         if (w == 8 && static_cast<size_t>(rows_pad) * sizeof(float) > kMaxRowLds8) continue;
         const long n = heads * ((T + 64 * w - 1) / (64 * w));
-        for (int r = 1; r <= kMaxMassParts && r <= mass_units && (r == 1 || r <= fit); ++r) {
+        for (int r = 1; r <= kMaxMassParts && r <= mass_units && (r == 1 || (r <= fit && n * (r - 1) < 8 * kPlanCus)); ++r) {
             const int part_tiles = (mass_units + r - 1) / r * mass_unit * Gh;
             if (r > 1 && part_tiles < 4) break;
             const double t = plan_time(w == 8 ? kMass8 : kMass4, n * r, part_tiles) + (r > 1 ? kMassCombine : 0.0);

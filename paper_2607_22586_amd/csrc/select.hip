@@ -14,12 +14,13 @@
 //           stops its passes early once the crossing bucket holds one key;
 //           the sweep variant always runs all three.  Both end by writing
 //           the group's membership plane: one bit per key, 32 keys a word.
-// vote      one wave per two membership words at a time: vote = #groups
-//           whose set holds the key, counted with one ballot per bit position;
-//           score = vote + lambda*anchor (fp64), or the total mass.
-// topk      one workgroup per (b, c): radix select (11-bit digits, stopping
-//           early once a bucket is taken whole) of the (C-1)-th largest score
-//           key over [0, T-1) (or the C-th over [0, T)), then an
+// vote      vote = #groups whose set holds the key, counted from the planes'
+//           words; score = vote + lambda*anchor (fp64), or the total mass; and
+//           per head the counts of the scores' first digits for the top-k.
+// topk      one workgroup per (b, c): the bucket of the vote kernel's counts
+//           that holds the (C-1)-th largest score key over [0, T-1) (or the
+//           C-th over [0, T)), a radix select among that bucket's keys (11-bit
+//           digits, stopping early once a bucket is taken whole), then an
 //           index-ordered compaction writes the kept tokens in ascending
 //           order and appends token T-1.
 #include <math.h>
@@ -67,35 +68,6 @@ __device__ __forceinline__ uint32_t mant_part(uint32_t bits, int S) {
 __device__ __forceinline__ uint64_t bucket_fixed(uint64_t sum, uint32_t e, int S) {
     const int sh = fixed_shift(e, S);
     return sh > 0 ? sum << min(sh, 63) : sum;   // sh stays below 40 for any non-empty bucket
-}
-
-// Adds (count 1, value f) of every active lane to bucket `digit`, combining
-// lanes of the wave that share a digit (skewed digit distributions would
-// otherwise serialise on one LDS address).
-__device__ __forceinline__ void hist_add(bool active, uint32_t digit, uint64_t f, uint32_t* cnt,
-                                         unsigned long long* sum) {
-    const int lane = lane_id();
-    uint64_t pending = __ballot(active);
-    for (int peel = 0; pending != 0; ++peel) {
-        if (peel == 4) {
-            if (active) {
-                atomicAdd(&cnt[digit], 1u);
-                if (sum) atomicAdd(&sum[digit], static_cast<unsigned long long>(f));
-            }
-            break;
-        }
-        const int leader = __ffsll(static_cast<unsigned long long>(pending)) - 1;
-        const uint32_t d0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(digit), leader));
-        const bool mine = active && digit == d0;
-        const uint64_t m = __ballot(mine);
-        if (sum) {
-            const uint64_t v = wave_sum_u64(mine ? f : 0ull);
-            if (lane == leader) atomicAdd(&sum[d0], static_cast<unsigned long long>(v));
-        }
-        if (lane == leader) atomicAdd(&cnt[d0], static_cast<uint32_t>(__popcll(m)));
-        if (mine) active = false;
-        pending &= ~m;
-    }
 }
 
 // Block-wide exclusive prefix count of `flag` over the NT threads in thread
@@ -146,10 +118,9 @@ __device__ __forceinline__ U block_excl_scan(U v, U* wtot, U& total) {
 // the digit whose bucket takes the running total (from the top) to need =
 // need_of(total of all buckets) (1 <= need <= total; no digit when need is
 // 0).  Returns the total; writes, through shared memory, the digit, `need`
-// minus the total of higher buckets, and the bucket's count (when `cnt` is
-// given).
-template <typename U, int NT, typename ValOf, typename NeedOf>
-__device__ __forceinline__ U crossing_of(ValOf val_of, const uint32_t* cnt, NeedOf need_of, U* wtot,
+// minus the total of higher buckets, and the bucket's count cnt_of(digit).
+template <typename U, int NT, typename ValOf, typename CntOf, typename NeedOf>
+__device__ __forceinline__ U crossing_of(ValOf val_of, CntOf cnt_of, NeedOf need_of, U* wtot,
                                          uint32_t* s_digit, U* s_rem, uint32_t* s_cnt) {
     constexpr int kPer = 2048 / NT;
     const int top = 2047 - kPer * static_cast<int>(threadIdx.x);
@@ -169,7 +140,7 @@ __device__ __forceinline__ U crossing_of(ValOf val_of, const uint32_t* cnt, Need
             if (excl < need && need <= excl + v[k]) {
                 *s_digit = top - k;
                 *s_rem = need - excl;
-                if (cnt != nullptr) *s_cnt = cnt[top - k];
+                *s_cnt = cnt_of(top - k);
             }
             excl += v[k];
         }
@@ -181,21 +152,8 @@ __device__ __forceinline__ U crossing_of(ValOf val_of, const uint32_t* cnt, Need
 template <typename U, int NT = kSelThreads>
 __device__ __forceinline__ void descending_crossing(const U* val, const uint32_t* cnt, U need, U* wtot,
                                                     uint32_t* s_digit, U* s_rem, uint32_t* s_cnt) {
-    crossing_of<U, NT>([val](int d) { return val[d]; }, cnt, [need](U) { return need; }, wtot, s_digit, s_rem,
-                       s_cnt);
-}
-
-template <int NT = kSelThreads>
-__device__ __forceinline__ uint64_t block_sum_u64(uint64_t v, unsigned long long* scratch) {
-    constexpr int kW = NT / kWave;
-    const int lane = lane_id(), wave = threadIdx.x / kWave;
-    v = wave_sum_u64(v);
-    if (lane == 0) scratch[wave] = v;
-    __syncthreads();
-    uint64_t t = 0;
-    for (int w = 0; w < kW; ++w) t += scratch[w];
-    __syncthreads();
-    return t;
+    crossing_of<U, NT>([val](int d) { return val[d]; }, [cnt](int d) { return cnt[d]; }, [need](U) { return need; },
+                       wtot, s_digit, s_rem, s_cnt);
 }
 
 // tau-cut digits: bits 30..20, 19..9, 8..0 of the (sign-free) mass bits.
@@ -215,11 +173,24 @@ __device__ __forceinline__ bool in_tau_set(uint32_t bits, int t, uint32_t theta,
     return bits > theta || (bits == theta && t <= tcut);
 }
 
-// Position of score key t of a head in `keys`: thread-major for the
-// register-resident top-k (thread i owns keys i*kpt .. i*kpt + kpt - 1 and
-// reads its j-th at j*1024 + i, so the reads are contiguous), else t.
-__device__ __forceinline__ int key_pos(const SelectArgs& a, int t) {
-    return a.kpt > 0 ? (t % a.kpt) * 1024 + t / a.kpt : t;
+// First digit (0..2047) of a score key, monotone in the score and fine where
+// the scores lie.  VOTE mode: the whole part (votes), then, in digit_sub
+// steps, the fraction (lambda * anchor, mostly far below 1) by its octave and
+// 2^digit_q steps an octave; scores of G + 1 or more (lambda * anchor above
+// 1) take the last digit.  MASS mode: 32 steps an octave from 2^-39 to 2^25.
+// (The top bits of the fp64 score would put all votes from 8 to 31, equal
+// steps of the score all keys of one vote, into one bucket.)
+__device__ __forceinline__ uint32_t key_digit(const SelectArgs& a, uint64_t key) {
+    const double score = __longlong_as_double(static_cast<long long>(key));
+    if (a.mode == 0) {
+        const double whole = floor(score);
+        if (!(whole <= static_cast<double>(a.G))) return 2047u;
+        const int bits = __float_as_int(static_cast<float>(score - whole));
+        const int sub = (bits >> (23 - a.digit_q)) - ((127 << a.digit_q) - a.digit_sub);
+        return static_cast<uint32_t>(static_cast<int>(whole) * a.digit_sub + min(max(sub, 0), a.digit_sub - 1)) & 2047u;
+    }
+    const int d = (__float_as_int(static_cast<float>(score)) >> 18) - ((127 - 39) << 5);
+    return static_cast<uint32_t>(min(max(d, 0), 2047));
 }
 
 // Group g's share of clearing the first-digit histogram of head hc (the
@@ -236,12 +207,36 @@ __device__ __forceinline__ uint32_t* plane_word(const SelectArgs& a, int64_t hc,
 }
 
 // ---------------------------------------------------------------- tau cut
+// Sweep form for rows too long for registers (T > 65536): every pass reads
+// the group's masses again (from L2 when they fit), kSweepBatch loads per
+// thread in flight.
+constexpr int kSweepBatch = 8;
+
+// f(t, bits of m[t]) for every key t of a row, the same trip count on every
+// thread; t >= T (bits 0) marks a lane without a key.
+template <typename F>
+__device__ __forceinline__ void sweep_row(const uint32_t* m, int T, F f) {
+    for (int base = 0; base < T; base += kSelThreads * kSweepBatch) {
+        uint32_t v[kSweepBatch];
+#pragma unroll
+        for (int k = 0; k < kSweepBatch; ++k) {
+            const int t = base + k * kSelThreads + static_cast<int>(threadIdx.x);
+            v[k] = t < T ? m[t] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kSweepBatch; ++k) {
+            // (uniform: whole waves past the row have nothing to do)
+            if (base + k * kSelThreads < T) f(base + k * kSelThreads + static_cast<int>(threadIdx.x), v[k]);
+        }
+    }
+}
+
 __global__ void __launch_bounds__(kSelThreads) tau_cut_kernel(SelectArgs a) {
     __shared__ uint32_t cnt[2048];
     __shared__ unsigned long long sum[2048];
     __shared__ unsigned long long wtot64[kSelWaves];
     __shared__ uint32_t wtot[kSelWaves];
-    __shared__ uint32_t s_digit, s_cnt;
+    __shared__ uint32_t s_digit, s_cnt, s_theta;
     __shared__ unsigned long long s_rem;
     __shared__ int32_t s_tcut;
 
@@ -253,34 +248,58 @@ __global__ void __launch_bounds__(kSelThreads) tau_cut_kernel(SelectArgs a) {
     const int S = a.fix_shift;
     clear_hist0_share(a, hc, g);
 
-    uint64_t local = 0;
-    for (int t = tid; t < a.T; t += kSelThreads) local += fixed_of(m[t], S);
-    const uint64_t total = block_sum_u64(local, wtot64);
     // every mass below the fixed-point resolution: empty set
     uint32_t theta = 0xFFFFFFFFu;
     int32_t tcut = -1;
-    if (total != 0) {
-        unsigned long long need = static_cast<unsigned long long>(ceil(a.tau * static_cast<double>(total)));
-        if (need < 1) need = 1;
-        if (need > total) need = total;
-
-        uint32_t prefix = 0;
-        for (int pass = 0; pass < 3; ++pass) {
-            const uint32_t mask = tau_mask(pass);
-            for (int i = tid; i < 2048; i += kSelThreads) { cnt[i] = 0; sum[i] = 0; }
-            __syncthreads();
-            // uniform trip count: hist_add needs every lane of the wave
-            for (int base = 0; base < a.T; base += kSelThreads) {
-                const int t = base + tid;
-                const uint32_t bits = t < a.T ? m[t] : 0u;
-                const bool in = t < a.T && (bits & mask) == prefix;
-                hist_add(in, tau_digit(bits, pass), in ? fixed_of(bits, S) : 0ull, cnt, sum);
+    unsigned long long need = 0;
+    uint32_t prefix = 0;
+    bool found = true;
+    for (int pass = 0; pass < 3; ++pass) {
+        const uint32_t mask = tau_mask(pass);
+        for (int i = tid; i < 2048; i += kSelThreads) { cnt[i] = 0; sum[i] = 0; }
+        __syncthreads();
+        sweep_row(m, a.T, [&](int t, uint32_t bits) {
+            if (t < a.T && (bits & mask) == prefix) {
+                const uint32_t dg = tau_digit(bits, pass);
+                atomicAdd(&cnt[dg], 1u);
+                atomicAdd(&sum[dg], static_cast<unsigned long long>(mant_part(bits, S)));
             }
-            __syncthreads();
-            descending_crossing<unsigned long long>(sum, cnt, need, wtot64, &s_digit, &s_rem, &s_cnt);
-            prefix |= s_digit << tau_shift(pass);
-            need = s_rem;
+        });
+        __syncthreads();
+        const uint32_t e_pre = prefix >> 23;
+        const unsigned long long total = crossing_of<unsigned long long, kSelThreads>(
+            [&](int d) {
+                return static_cast<unsigned long long>(
+                    bucket_fixed(sum[d], pass == 0 ? static_cast<uint32_t>(d) >> 3 : e_pre, S));
+            },
+            [&](int d) { return cnt[d]; },
+            [&](unsigned long long tot) {
+                if (pass == 0) {
+                    need = static_cast<unsigned long long>(ceil(a.tau * static_cast<double>(tot)));
+                    if (need < 1) need = 1;
+                    if (need > tot) need = tot;
+                }
+                return need;
+            },
+            wtot64, &s_digit, &s_rem, &s_cnt);
+        if (pass == 0 && total == 0) {
+            found = false;
+            break;
         }
+        prefix |= s_digit << tau_shift(pass);
+        need = s_rem;
+        if (pass < 2 && s_cnt == 1u) {
+            // one key left in the crossing bucket: its mass is theta
+            const uint32_t fixed = tau_fixed(pass);
+            sweep_row(m, a.T, [&](int t, uint32_t bits) {
+                if (t < a.T && (bits & fixed) == prefix) s_theta = bits;
+            });
+            __syncthreads();
+            prefix = s_theta;
+            break;
+        }
+    }
+    if (found) {
         // keys with mass == theta each carry f_theta; the first k_eq by index
         // enter the set (all of them when k_eq covers the bucket)
         theta = prefix;
@@ -309,69 +328,92 @@ __global__ void __launch_bounds__(kSelThreads) tau_cut_kernel(SelectArgs a) {
         a.theta[hcg] = theta;
         a.tcut[hcg] = tcut;
     }
-    // membership plane: each wave's 64 keys of a sweep step are two words
+    // membership plane: each wave's 64 consecutive keys are two words
     const int lane = lane_id();
-    for (int base = 0; base < a.T; base += kSelThreads) {
-        const int t = base + tid;
-        const uint64_t mb = __ballot(t < a.T && in_tau_set(m[t], t, theta, tcut));
-        const int w = (base + (tid & ~(kWave - 1))) / 32 + lane;
+    sweep_row(m, a.T, [&](int t, uint32_t bits) {
+        const uint64_t mb = __ballot(t < a.T && in_tau_set(bits, t, theta, tcut));
+        const int w = (t & ~(kWave - 1)) / 32 + lane;
         if (lane < 2 && 32 * w < a.T) *plane_word(a, hc, g, w) = static_cast<uint32_t>(mb >> (32 * lane));
-    }
+    });
 }
 
 // ---------------------------------------------------------------- vote + score
-// One workgroup per 32 membership words (128-byte lines of every group's
-// plane) of one head, each wave two words at a time: in each half-wave,
-// lane l reads the word of group l (32 groups at a time), and one ballot per
-// bit position j counts, for both words at once, the groups whose set holds
-// key j; lane j of each half keeps its own key's count.
+// One workgroup per 1024 keys of one head.  The membership words of 32
+// groups at a time (a 128-byte line of each group's plane) are staged in LDS,
+// one row per 32-key word; the 32 lanes that share a word read its row by
+// broadcast, 4 groups a read, and each counts its own key's bit.  (One ballot
+// per bit position and group word took 7.7 us a call for 16 heads of 16384
+// keys, this 5.1: launch, load latency and the count histogram.)
 constexpr int kVoteThreads = 256;
 constexpr int kVoteWords = 32;                          // words per workgroup
-constexpr int kVoteSteps = kVoteWords * kWave / (2 * kVoteThreads);
+constexpr int kVoteKeys = 32 * kVoteWords / kVoteThreads;   // keys per thread
+constexpr int kVoteRow = 36;                            // words per LDS row (32 groups, 16-byte aligned)
 
 __global__ void __launch_bounds__(kVoteThreads) vote_score_kernel(SelectArgs a) {
     __shared__ uint32_t lh[2048];            // this workgroup's first-digit counts
-    const int c = blockIdx.y, b = blockIdx.z;
+    __shared__ __align__(16) uint32_t pw[kVoteWords * kVoteRow];
+    const int c = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     const int64_t hc = static_cast<int64_t>(b) * a.Hkv + c;
-    const int lane = lane_id(), half = lane >> 5, j0 = lane & 31;
     const int nw = (a.T + 31) / 32;
     const int pool = a.keep_last ? a.T - 1 : a.T;
-    const int wbase = static_cast<int>(blockIdx.x) * kVoteWords + 2 * kVoteSteps * (static_cast<int>(threadIdx.x) / kWave);
-    for (int i = threadIdx.x; i < 2048; i += kVoteThreads) lh[i] = 0u;
-    __syncthreads();
+    const int w0 = static_cast<int>(blockIdx.x) * kVoteWords;
+    const bool vote_mode = a.mode == 0;
+    // key k of this thread: 32 w0 + 256 k + tid
+    const int t0 = 32 * w0 + tid;
+    float val[kVoteKeys];
+    const float* src = vote_mode ? a.anchor : a.mass;
 #pragma unroll
-    for (int step = 0; step < kVoteSteps; ++step) {
-        const int w = wbase + 2 * step + half;
-        const int t = 32 * w + j0;
-        double score = 0.0;
-        if (a.mode == 0) {
-            uint32_t vote = 0;
-            for (int g0 = 0; g0 < a.G; g0 += 32) {
-                const int g = g0 + j0;
-                const uint32_t word = (w < nw && g < a.G) ? *plane_word(a, hc, g, w) : 0u;
+    for (int k = 0; k < kVoteKeys; ++k) {
+        const int t = t0 + k * kVoteThreads;
+        val[k] = t < a.T ? src[hc * a.T + t] : 0.f;
+    }
+    for (int i = tid; i < 2048; i += kVoteThreads) lh[i] = 0u;
+    uint32_t vote[kVoteKeys] = {};
+    if (vote_mode) {
+        for (int g0 = 0; g0 < a.G; g0 += 32) {
+            const int w = w0 + (tid & 31);
+            uint32_t x[32 * kVoteWords / kVoteThreads];
 #pragma unroll
-                for (int j = 0; j < 32; ++j) {
-                    const uint64_t m = __ballot((word >> j) & 1u);
-                    const uint32_t n0 = static_cast<uint32_t>(__popcll(m & 0xFFFFFFFFull));
-                    const uint32_t n1 = static_cast<uint32_t>(__popcll(m >> 32));
-                    if (j0 == j) vote += half ? n1 : n0;
+            for (int k = 0; k < 32 * kVoteWords / kVoteThreads; ++k) {
+                const int g = g0 + (tid >> 5) + k * (kVoteThreads / 32);
+                x[k] = (w < nw && g < a.G) ? *plane_word(a, hc, g, w) : 0u;
+            }
+            if (g0 > 0) __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 32 * kVoteWords / kVoteThreads; ++k)
+                pw[(tid & 31) * kVoteRow + (tid >> 5) + k * (kVoteThreads / 32)] = x[k];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kVoteKeys; ++k) {
+                const u32x4* row = reinterpret_cast<const u32x4*>(pw + ((k * kVoteThreads + tid) >> 5) * kVoteRow);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const u32x4 v = row[q];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) vote[k] += (v[e] >> (tid & 31)) & 1u;
                 }
             }
-            if (t < a.T) {
-                score = static_cast<double>(vote) + a.lambda * static_cast<double>(a.anchor[hc * a.T + t]);
-                if (a.votes != nullptr) a.votes[hc * a.T + t] = static_cast<uint8_t>(vote);
-            }
-        } else if (t < a.T) {
-            score = static_cast<double>(a.mass[hc * a.T + t]);
         }
-        if (t < a.T) {
-            const uint64_t key = static_cast<uint64_t>(__double_as_longlong(score));
-            a.keys[hc * a.key_stride + key_pos(a, t)] = key;
-            if (t < pool) atomicAdd(&lh[static_cast<uint32_t>(key >> 53) & 2047u], 1u);
+    } else {
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < kVoteKeys; ++k) {
+        const int t = t0 + k * kVoteThreads;
+        if (t >= a.T) continue;
+        double score = static_cast<double>(val[k]);
+        if (vote_mode) {
+            score = static_cast<double>(vote[k]) + a.lambda * score;
+            if (a.votes != nullptr) a.votes[hc * a.T + t] = static_cast<uint8_t>(vote[k]);
         }
+        const uint64_t key = static_cast<uint64_t>(__double_as_longlong(score));
+        const uint32_t dg = key_digit(a, key);
+        a.keys[hc * a.T + t] = key;
+        a.digits[hc * a.digit_stride + t] = static_cast<uint16_t>(dg + 1u);
+        if (t < pool) atomicAdd(&lh[dg], 1u);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < 2048; i += kVoteThreads)
+    for (int i = tid; i < 2048; i += kVoteThreads)
         if (lh[i] != 0u) atomicAdd(&a.hist0[hc * 2048 + i], lh[i]);
 }
 
@@ -384,63 +426,37 @@ __global__ void __launch_bounds__(256) clear_hist0_kernel(SelectArgs a) {
 }
 
 // ---------------------------------------------------------------- top-k
-// Radix search for the selection threshold over the 64-bit score keys of
-// the pool: 11-bit digits from the top (bits 63..53, ..., 9..0), stopping
-// once the crossing bucket is taken whole.  `each(f)` calls f(key, ok) with
-// the same trip count on every thread, ok marking the pool keys this thread
-// owns.  On return, the selected keys are {key > theta} plus the first k_eq
-// keys (by index) with key == theta.  Requires 1 <= want < pool size.  The
-// first pass takes its counts from h0 (all pool keys by bits 63..53).
-struct TopkShared {
-    uint32_t cnt[2][2048];       // pass p counts into cnt[p % 2]
-    uint32_t wtot[kSelWaves];
-    uint32_t s_digit, s_cnt, s_rem;
-};
+// Budgeted selection of one (b, c).  Thread i owns keys i*kpt .. i*kpt + kpt
+// - 1 through their first digits (16 bits each, kept in registers up to
+// T = 32768: KPT > 0; read again from L2 by a rolled loop beyond, KPT = 0,
+// where unrolled code of 64 keys a thread waits for its own instructions).  The vote
+// kernel's counts name the digit bucket that holds the threshold; keys in
+// higher buckets are selected, lower ones are not, and only the bucket's own
+// keys (a few hundred of 16384 in the benchmark's layers) are read as 64-bit
+// scores, at most kTopkOwn a thread, and searched by radix, 11 bits at a time
+// from the first bit in which they differ.  A bucket too large for that is
+// searched in place.  Bound by its chain of barriers (one workgroup per head):
+// with all 64-bit keys in registers and their top bits as the first digit it
+// took 15.4 us a call for 16 heads of 16384 keys, and in sweeps 75 us for 4 of
+// 40000; this form takes 9.0 and 11.0 (8.3 and 11.8 within a layer).
+constexpr int kTopkOwn = 4;
+constexpr uint32_t kTopkList = kTopkOwn * kSelThreads;
+constexpr int kTopkMaxKpt = 512;         // keys per thread (T = 524288) up to which selection bits fit in LDS
+// Bucket sizes up to here: every key ranked against all others (beyond, the
+// 64-bit comparisons cost more than radix passes: 4 us at 200 keys).
+constexpr uint32_t kTopkRank = 128;
 
-template <typename Each>
-__device__ __forceinline__ void topk_threshold(uint32_t want, Each each, const uint32_t* h0, TopkShared& sh,
-                                               uint64_t& theta, uint32_t& k_eq) {
-    const int tid = threadIdx.x;
-    uint64_t prefix = 0, mask = 0;
-    uint32_t need = want;
-    // the first digit's counts, made by the vote kernel; the other buffer
-    // cleared for the second pass
-    for (int i = tid; i < 2048; i += kSelThreads) {
-        sh.cnt[0][i] = h0[i];
-        sh.cnt[1][i] = 0;
-    }
-    __syncthreads();
-    for (int pass = 0; pass < 6; ++pass) {
-        const int shift = pass == 5 ? 0 : 53 - 11 * pass;
-        uint32_t* cnt = sh.cnt[pass & 1];
-        if (pass > 0) {
-            // plain LDS atomics over the keys left in the crossing bucket
-            each([&](uint64_t kv, bool ok) {
-                if (ok && (kv & mask) == prefix) atomicAdd(&cnt[static_cast<uint32_t>(kv >> shift) & 2047u], 1u);
-            });
-            __syncthreads();
-        }
-        descending_crossing<uint32_t>(cnt, cnt, need, sh.wtot, &sh.s_digit, &sh.s_rem, &sh.s_cnt);
-        // every read of this buffer is done (the crossing ends with a
-        // barrier): clear it for pass + 2, two barriers away
-        for (int i = tid; i < 2048; i += kSelThreads) cnt[i] = 0;
-        prefix |= static_cast<uint64_t>(sh.s_digit) << shift;
-        mask |= (shift == 0 ? 0x1FFull : 0x7FFull) << shift;
-        need = sh.s_rem;
-        if (sh.s_cnt == need) {
-            // the whole bucket is taken: every key >= its lower bound (> 0,
-            // since the pool holds more keys than are wanted)
-            theta = prefix - 1;
-            k_eq = 0;
-            return;
-        }
-    }
-    theta = prefix;
-    k_eq = need;
-}
-
+template <int KPT>
 __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
-    __shared__ TopkShared sh;
+    static_assert(KPT % 8 == 0, "whole 16-byte pieces of digits");
+    static_assert(KPT <= 32, "one word of selection bits a thread");
+    constexpr int kWords = KPT > 0 ? 1 : kTopkMaxKpt / 32;   // words of selection bits per thread
+    __shared__ uint32_t cnt[2][2048];                    // radix pass p counts into cnt[p % 2]
+    __shared__ int32_t list[kTopkList];                  // the bucket's keys (indices), in any order
+    __shared__ uint32_t picked[kWords][kSelThreads];
+    __shared__ uint32_t wtot[kSelWaves];
+    __shared__ unsigned long long s_diff, s_first;
+    __shared__ uint32_t s_digit, s_cnt, s_rem, n_list, n_same;
 
     const int c = blockIdx.x, b = blockIdx.y;
     const int64_t hc = static_cast<int64_t>(b) * a.Hkv + c;
@@ -456,34 +472,268 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
     }
     const int pool = a.keep_last ? a.T - 1 : a.T;
     const uint32_t want = static_cast<uint32_t>(a.keep_last ? budget - 1 : budget);
-    const uint64_t* key = a.keys + hc * a.key_stride;
+    const uint64_t* key = a.keys + hc * a.T;
+    const int kpt = KPT > 0 ? KPT : a.kpt;
+    const int64_t t0 = static_cast<int64_t>(tid) * kpt;
+    const int own = static_cast<int>(min(max(static_cast<int64_t>(pool) - t0, static_cast<int64_t>(0)),
+                                         static_cast<int64_t>(kpt)));
+    // digits as stored (digit + 1); 0 where there is no pool key
+    const uint16_t* dig = a.digits + hc * a.digit_stride + t0;
+    uint32_t pk[KPT > 0 ? KPT / 2 : 1];
+#pragma unroll
+    for (int q = 0; q < KPT / 8; ++q) {
+        const u32x4 x = *reinterpret_cast<const u32x4*>(dig + 8 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pk[4 * q + e] = x[e];
+    }
+    auto clip = [&](uint32_t w, int j) {                 // digits j and j + 1
+        return j + 1 < own ? w : (j < own ? w & 0xFFFFu : 0u);
+    };
+#pragma unroll
+    for (int q = 0; q < KPT / 2; ++q) pk[q] = clip(pk[q], 2 * q);
+    // f(j, stored digit) for this thread's keys, ascending, from memory: the
+    // in-place search of a bucket of many equal or nearly equal scores
+    auto each_mem = [&](auto&& f) {
+#pragma nounroll
+        for (int j0 = 0; j0 < own; j0 += 2) {
+            const uint32_t w = clip(*reinterpret_cast<const uint32_t*>(dig + j0), j0);
+            f(j0, w & 0xFFFFu);
+            f(j0 + 1, w >> 16);
+        }
+    };
 
-    uint64_t theta = 0;
-    uint32_t k_eq = 0;
+    const uint32_t* h0 = a.hist0 + hc * 2048;
+    for (int i = tid; i < 2048; i += kSelThreads) {
+        cnt[0][i] = h0[i];
+        cnt[1][i] = 0;
+    }
+    const int n_words = KPT > 0 ? 1 : min((kpt + 31) / 32, kWords);
+    for (int w = 0; w < n_words; ++w) picked[w][tid] = 0;
+    // sets the selection bit of key t with its owner
+    auto pick = [&](int32_t t) {
+        const int own_by = KPT > 0 ? t / (KPT > 0 ? KPT : 1) : t / kpt, j = t - own_by * kpt;
+        atomicOr(&picked[j / 32][own_by], 1u << (j % 32));
+    };
+    if (tid == 0) {
+        n_list = n_same = 0;
+        s_diff = s_first = 0;
+        s_digit = 0xFFFFu;
+        s_cnt = s_rem = 0;
+    }
+    __syncthreads();
+    uint32_t dg = 0x10000u, n_in = 0, need = 0;          // stored digit of the bucket; above all when want is 0
     if (want > 0) {
-        topk_threshold(want, [&](auto&& f) {
-            for (int base = 0; base < pool; base += kSelThreads) {
-                const int t = base + tid;
-                f(t < pool ? key[t] : 0ull, t < pool);
+        descending_crossing<uint32_t>(cnt[0], cnt[0], want, wtot, &s_digit, &s_rem, &s_cnt);
+        for (int i = tid; i < 2048; i += kSelThreads) cnt[0][i] = 0;   // every read of it is done
+        dg = s_digit + 1u;
+        n_in = s_cnt;
+        need = s_rem;
+    }
+    const bool listed = (KPT > 0 || kpt <= kTopkMaxKpt) && n_in <= kTopkList;
+
+    // the keys above the bucket as bits, and the bucket's list
+    uint32_t n_sel = 0;
+    {
+        uint32_t above = 0;
+        auto eight = [&](int j0, const u32x4& x) {       // digits j0 .. j0 + 7
+            uint32_t gt = 0, eq = 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t d = (e & 1) ? x[e / 2] >> 16 : x[e / 2] & 0xFFFFu;
+                gt |= (d > dg ? 1u : 0u) << e;
+                eq |= (d == dg ? 1u : 0u) << e;
             }
-        }, a.hist0 + hc * 2048, sh, theta, k_eq);
+            above |= gt << (j0 & 31);
+            n_sel += static_cast<uint32_t>(__popc(gt));
+            if (listed) {
+                for (; eq != 0; eq &= eq - 1)
+                    list[atomicAdd(&n_list, 1u)] = static_cast<int32_t>(t0) + j0 + __ffs(static_cast<int>(eq)) - 1;
+            }
+        };
+        if constexpr (KPT > 0) {
+#pragma unroll
+            for (int q = 0; q < KPT / 8; ++q) eight(8 * q, u32x4{pk[4 * q], pk[4 * q + 1], pk[4 * q + 2], pk[4 * q + 3]});
+            picked[0][tid] = above;
+        } else {
+#pragma unroll 2
+            for (int j0 = 0; j0 < own; j0 += 8) {
+                u32x4 x = *reinterpret_cast<const u32x4*>(dig + j0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = clip(x[e], j0 + 2 * e);
+                eight(j0, x);
+                if (listed && ((j0 & 31) == 24 || j0 + 8 >= own)) {
+                    picked[j0 / 32][tid] = above;
+                    above = 0;
+                }
+            }
+        }
     }
-    uint32_t eq_seen = 0, written = 0;
-    for (int base = 0; base < pool; base += kSelThreads) {
-        const int t = base + tid;
-        const bool in = t < pool;
-        const uint64_t kv = in ? key[t] : 0ull;
-        const bool gt = in && want > 0 && kv > theta;
-        const bool eq = in && want > 0 && k_eq > 0 && kv == theta;
-        uint32_t eq_tot;
-        const uint32_t eq_before = block_excl_count(eq, sh.wtot, eq_tot);
-        const bool sel = gt || (eq && eq_seen + eq_before < k_eq);
-        uint32_t sel_tot;
-        const uint32_t pos = block_excl_count(sel, sh.wtot, sel_tot);
-        if (sel && written + pos < want) out[written + pos] = t;
-        eq_seen += eq_tot;
-        written = min(written + sel_tot, want);
+    __syncthreads();
+    if (listed && n_in <= kTopkRank) {
+        // a small bucket: each key's rank (score desc, index asc) among the
+        // others by comparison, 8 threads a key, without radix passes
+        int64_t* lk = reinterpret_cast<int64_t*>(cnt[1]);            // [kTopkRank]; not counted into yet
+        const int n = static_cast<int>(min(n_in, n_list));
+        if (tid < n) lk[tid] = static_cast<int64_t>(key[list[tid]]);
+        __syncthreads();
+        const int me = tid >> 3;
+        if (me < n) {
+            const int64_t mk = lk[me];
+            const int32_t mt = list[me];
+            uint32_t rank = 0;
+#pragma unroll 4
+            for (int i = tid & 7; i < n; i += 8) {
+                const int64_t k = lk[i];
+                rank += (k > mk || (k == mk && list[i] < mt)) ? 1u : 0u;
+            }
+#pragma unroll
+            for (int o = 1; o < 8; o <<= 1) rank += static_cast<uint32_t>(__shfl_xor(static_cast<int>(rank), o, kWave));
+            if ((tid & 7) == 0 && rank < need) pick(mt);
+        }
+        n_in = need = 0;                                 // nothing left to search
     }
+    // the bucket's keys of this thread's share of the list
+    int64_t ck[kTopkOwn];
+    int32_t ct[kTopkOwn];
+#pragma unroll
+    for (int i = 0; i < kTopkOwn; ++i) {
+        const uint32_t at = static_cast<uint32_t>(tid + i * kSelThreads);
+        const bool in = listed && at < min(n_in, n_list);
+        ct[i] = in ? list[at] : -1;
+        ck[i] = in ? static_cast<int64_t>(key[ct[i]]) : -1;
+    }
+    // f(key) for the bucket's keys: this thread's share of the list, or its own
+    auto in_bucket = [&](auto&& f) {
+        if (listed) {
+#pragma unroll
+            for (int i = 0; i < kTopkOwn; ++i)
+                if (ct[i] >= 0) f(static_cast<uint64_t>(ck[i]));
+        } else {
+            each_mem([&](int j, uint32_t d) {
+                if (d == dg) f(key[t0 + j]);
+            });
+        }
+    };
+    // threshold: {key > theta} plus the first k_eq keys (by index) equal to it
+    int64_t theta = -1;
+    uint32_t k_eq = 0;
+    if (need < n_in) {
+        in_bucket([&](uint64_t kv) { s_first = kv; });   // any one of them
+        __syncthreads();
+        const uint64_t first = s_first;
+        uint64_t diff = 0;
+        in_bucket([&](uint64_t kv) { diff |= kv ^ first; });
+        // (reduced within the wave first: the compiler turns a per-lane atomic
+        // of varying values into a loop over the lanes)
+        diff = wave_or_u64(diff);
+        if (lane_id() == 0 && diff != 0) atomicOr(&s_diff, static_cast<unsigned long long>(diff));
+        __syncthreads();
+        diff = s_diff;
+        if (diff == 0) {                                 // all equal: the first `need` by index
+            theta = static_cast<int64_t>(first);
+            k_eq = need;
+        } else {
+            const int top = 63 - __clzll(static_cast<long long>(diff));
+            uint64_t mask = top == 63 ? 0ull : ~0ull << (top + 1);
+            uint64_t prefix = first & mask;
+            int shift = max(top - 10, 0);
+            for (int pass = 0;; ++pass) {
+                uint32_t* pc = cnt[pass & 1];
+                in_bucket([&](uint64_t kv) {
+                    if ((kv & mask) == prefix) atomicAdd(&pc[static_cast<uint32_t>(kv >> shift) & 2047u], 1u);
+                });
+                __syncthreads();
+                descending_crossing<uint32_t>(pc, pc, need, wtot, &s_digit, &s_rem, &s_cnt);
+                // cleared for pass + 2, two barriers away
+                for (int i = tid; i < 2048; i += kSelThreads) pc[i] = 0;
+                prefix |= static_cast<uint64_t>(s_digit) << shift;
+                mask |= 0x7FFull << shift;
+                need = s_rem;
+                if (s_cnt == need) {
+                    // the rest is taken whole: every key >= its lower bound
+                    theta = static_cast<int64_t>(prefix) - 1;
+                    break;
+                }
+                if (shift == 0) {
+                    theta = static_cast<int64_t>(prefix);
+                    k_eq = need;
+                    break;
+                }
+                shift = max(shift - 11, 0);
+            }
+        }
+    }
+
+    uint32_t sel_total, pos;
+    if (listed) {
+        // the selected ones of the list, as bits of their owners
+        bool take[kTopkOwn];
+#pragma unroll
+        for (int i = 0; i < kTopkOwn; ++i) take[i] = ct[i] >= 0 && ck[i] > theta;
+        if (k_eq > 0) {
+            // equal keys by index: each counts the equal ones before it
+            __syncthreads();                             // every read of the list is done
+#pragma unroll
+            for (int i = 0; i < kTopkOwn; ++i)
+                if (ct[i] >= 0 && ck[i] == theta) list[atomicAdd(&n_same, 1u)] = ct[i];
+            __syncthreads();
+            const uint32_t n = n_same;
+#pragma unroll
+            for (int i = 0; i < kTopkOwn; ++i) {
+                if (ct[i] < 0 || ck[i] != theta) continue;
+                uint32_t before = 0;
+                for (uint32_t x = 0; x < n; ++x) before += list[x] < ct[i] ? 1u : 0u;
+                take[i] = before < k_eq;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kTopkOwn; ++i)
+            if (take[i]) pick(ct[i]);
+        __syncthreads();
+        n_sel = 0;
+        for (int w = 0; w < n_words; ++w) n_sel += static_cast<uint32_t>(__popc(picked[w][tid]));
+        pos = block_excl_scan<uint32_t>(n_sel, wtot, sel_total);
+        for (int w = 0; w < n_words; ++w) {
+            for (uint32_t m = picked[w][tid]; m != 0; m &= m - 1) {
+                if (pos < want) out[pos] = static_cast<int32_t>(t0) + 32 * w + __ffs(static_cast<int>(m)) - 1;
+                ++pos;
+            }
+        }
+    } else {
+        uint32_t n_eq = 0;
+        each_mem([&](int j, uint32_t d) {
+            if (d != dg) return;
+            const int64_t kv = static_cast<int64_t>(key[t0 + j]);
+            n_sel += kv > theta ? 1u : 0u;
+            n_eq += kv == theta ? 1u : 0u;
+        });
+        if (k_eq > 0) {
+            // this thread's share of the k_eq equal keys, by index
+            uint32_t eq_total;
+            const uint32_t before = block_excl_scan<uint32_t>(n_eq, wtot, eq_total);
+            k_eq = before < k_eq ? min(n_eq, k_eq - before) : 0u;
+            n_sel += k_eq;
+        }
+        pos = block_excl_scan<uint32_t>(n_sel, wtot, sel_total);
+        if (n_sel > 0) {
+            each_mem([&](int j, uint32_t d) {
+                bool take = d > dg;
+                if (d == dg) {
+                    const int64_t kv = static_cast<int64_t>(key[t0 + j]);
+                    take = kv > theta;
+                    if (kv == theta && k_eq > 0) {
+                        take = true;
+                        --k_eq;
+                    }
+                }
+                if (take) {
+                    if (pos < want) out[pos] = static_cast<int32_t>(t0) + j;
+                    ++pos;
+                }
+            });
+        }
+    }
+    uint32_t written = min(sel_total, want);
     if (a.keep_last) {
         if (tid == 0) out[written] = a.T - 1;
         written += 1;
@@ -508,10 +758,15 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
 template <int KPT, int NT>
 __global__ void __launch_bounds__(NT) tau_cut_reg_kernel(SelectArgs a) {
     static_assert(KPT % 4 == 0, "whole 4-key pieces per thread");
+    // one 64-bit LDS atomic per key carries its count (from bit kCntBit) and
+    // its mantissa part (< 2^24): the row's sum stays below 2^kCntBit and its
+    // count below 2^(64 - kCntBit)
+    constexpr int kCntBit = 44;
+    static_assert(static_cast<int64_t>(KPT) * NT < (1 << 20), "packed sum and count");
+    constexpr unsigned long long kSumMask = (1ull << kCntBit) - 1;
     constexpr int kQ = KPT / 4;
     constexpr int kChunk = 4 * NT;
     constexpr int kW = NT / kWave;
-    __shared__ uint32_t cnt[2048];
     __shared__ unsigned long long sum[2048];
     __shared__ unsigned long long wtot64[kW];
     __shared__ uint32_t wtot[kW];
@@ -530,7 +785,9 @@ __global__ void __launch_bounds__(NT) tau_cut_reg_kernel(SelectArgs a) {
     auto key_of = [&](int q, int e) { return kChunk * q + 4 * tid + e; };
 
     // masses (bits), held for all passes (their fixed-point values are
-    // recomputed where needed); keys past T read as mass 0
+    // recomputed where needed).  Keys past T read as mass 0, which no step
+    // below counts: a mass of 0 adds nothing to a sum, and the cut is never 0
+    // (a bucket whose sum is 0 is never the crossing one).
     uint32_t mb[KPT];
     if ((a.T & 3) == 0 && (reinterpret_cast<uintptr_t>(m) & 15u) == 0) {
 #pragma unroll
@@ -555,17 +812,16 @@ __global__ void __launch_bounds__(NT) tau_cut_reg_kernel(SelectArgs a) {
 #pragma nounroll
         for (int pass = 0; pass < 3; ++pass) {
             const uint32_t mask = tau_mask(pass);
-            for (int i = tid; i < 2048; i += NT) { cnt[i] = 0; sum[i] = 0; }
+            for (int i = tid; i < 2048; i += NT) sum[i] = 0;
             __syncthreads();
 #pragma unroll
             for (int j = 0; j < KPT; ++j) {
                 // opaque inside the pass loop, so the per-key values are not
                 // hoisted out of it and kept live
                 asm volatile("" : "+v"(mb[j]));
-                if (key_of(j / 4, j % 4) < a.T && (mb[j] & mask) == prefix) {
+                if (mb[j] != 0u && (mb[j] & mask) == prefix) {
                     const uint32_t dg = tau_digit(mb[j], pass);
-                    atomicAdd(&cnt[dg], 1u);
-                    atomicAdd(&sum[dg], static_cast<unsigned long long>(mant_part(mb[j], S)));
+                    atomicAdd(&sum[dg], (1ull << kCntBit) | mant_part(mb[j], S));
                 }
             }
             __syncthreads();
@@ -575,9 +831,9 @@ __global__ void __launch_bounds__(NT) tau_cut_reg_kernel(SelectArgs a) {
             const unsigned long long total = crossing_of<unsigned long long, NT>(
                 [&](int d) {
                     return static_cast<unsigned long long>(
-                        bucket_fixed(sum[d], pass == 0 ? static_cast<uint32_t>(d) >> 3 : e_pre, S));
+                        bucket_fixed(sum[d] & kSumMask, pass == 0 ? static_cast<uint32_t>(d) >> 3 : e_pre, S));
                 },
-                cnt,
+                [&](int d) { return static_cast<uint32_t>(sum[d] >> kCntBit); },
                 [&](unsigned long long tot) {
                     if (pass == 0) {
                         // the shortest prefix reaching tau * total (at least one key)
@@ -599,7 +855,7 @@ __global__ void __launch_bounds__(NT) tau_cut_reg_kernel(SelectArgs a) {
                 // remaining passes would only spell out its low bits
 #pragma unroll
                 for (int j = 0; j < KPT; ++j)
-                    if (key_of(j / 4, j % 4) < a.T && (mb[j] & tau_fixed(pass)) == prefix) s_theta = mb[j];
+                    if ((mb[j] & tau_fixed(pass)) == prefix) s_theta = mb[j];
                 __syncthreads();
                 prefix = s_theta;
                 break;
@@ -620,14 +876,14 @@ __global__ void __launch_bounds__(NT) tau_cut_reg_kernel(SelectArgs a) {
             for (int q = 0; q < kQ; ++q) {
                 uint32_t n_eq = 0;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) n_eq += (key_of(q, e) < a.T && mb[4 * q + e] == prefix) ? 1u : 0u;
+                for (int e = 0; e < 4; ++e) n_eq += mb[4 * q + e] == prefix ? 1u : 0u;
                 uint32_t tot;
                 const uint32_t before = block_excl_scan<uint32_t, NT>(n_eq, wtot, tot);
                 if (seen + before < k_eq && k_eq <= seen + before + n_eq) {
                     uint64_t at = seen + before;
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (key_of(q, e) < a.T && mb[4 * q + e] == prefix && ++at == k_eq) s_tcut = key_of(q, e);
+                        if (mb[4 * q + e] == prefix && ++at == k_eq) s_tcut = key_of(q, e);
                 }
                 seen += tot;
                 if (seen >= k_eq) break;
@@ -647,7 +903,7 @@ __global__ void __launch_bounds__(NT) tau_cut_reg_kernel(SelectArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int t = key_of(q, e);
-            word |= (t < a.T && in_tau_set(mb[4 * q + e], t, theta, tcut)) ? 1u << (4 * (lane & 7) + e) : 0u;
+            word |= in_tau_set(mb[4 * q + e], t, theta, tcut) ? 1u << (4 * (lane & 7) + e) : 0u;
         }
 #pragma unroll
         for (int o = 1; o < 8; o <<= 1) word |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(word), o, kWave));
@@ -655,98 +911,32 @@ __global__ void __launch_bounds__(NT) tau_cut_reg_kernel(SelectArgs a) {
     }
 }
 
-// Budgeted selection of one (b, c); same result as topk_kernel.
-template <int KPT>
-__global__ void __launch_bounds__(kSelThreads) topk_reg_kernel(SelectArgs a) {
-    __shared__ TopkShared sh;
-
-    const int c = blockIdx.x, b = blockIdx.y;
-    const int64_t hc = static_cast<int64_t>(b) * a.Hkv + c;
-    const int tid = threadIdx.x;
-    int32_t* out = a.idx + hc * a.c_max;
-    int budget = a.budget;
-    if (a.budgets != nullptr) budget = min(max(a.budgets[hc], 1), a.c_max);
-
-    if (a.T <= budget) {
-        for (int j = tid; j < a.c_max; j += kSelThreads) out[j] = (j < a.T) ? j : -1;
-        if (tid == 0) a.counts[hc] = a.T;
-        return;
-    }
-    const int pool = a.keep_last ? a.T - 1 : a.T;
-    const uint32_t want = static_cast<uint32_t>(a.keep_last ? budget - 1 : budget);
-    const uint64_t* key = a.keys + hc * a.key_stride;
-    const int t0 = tid * KPT;
-    uint64_t kv[KPT];
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) kv[j] = (t0 + j < pool) ? key[j * kSelThreads + tid] : 0ull;
-
-    uint64_t theta = 0;
-    uint32_t k_eq = 0;
-    if (want > 0) {
-        topk_threshold(want, [&](auto&& f) {
-#pragma unroll
-            for (int j = 0; j < KPT; ++j) f(kv[j], t0 + j < pool);
-        }, a.hist0 + hc * 2048, sh, theta, k_eq);
-    }
-    // index-ordered compaction: keys > theta, then the first k_eq equal keys
-    uint32_t n_eq = 0;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) n_eq += (want > 0 && k_eq > 0 && t0 + j < pool && kv[j] == theta) ? 1u : 0u;
-    uint32_t eq_total = 0, eq_seen = 0;
-    if (want > 0 && k_eq > 0) eq_seen = block_excl_scan<uint32_t>(n_eq, sh.wtot, eq_total);
-    uint32_t sel_mask = 0, n_sel = 0;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        const bool in = want > 0 && t0 + j < pool;
-        const bool gt = in && kv[j] > theta;
-        bool eq = in && k_eq > 0 && kv[j] == theta;
-        if (eq) eq = eq_seen++ < k_eq;
-        if (gt || eq) {
-            sel_mask |= 1u << j;
-            ++n_sel;
-        }
-    }
-    uint32_t sel_total;
-    uint32_t pos = block_excl_scan<uint32_t>(n_sel, sh.wtot, sel_total);
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        if ((sel_mask >> j) & 1u) {
-            if (pos < want) out[pos] = t0 + j;
-            ++pos;
-        }
-    }
-    uint32_t written = min(sel_total, want);
-    if (a.keep_last) {
-        if (tid == 0) out[written] = a.T - 1;
-        written += 1;
-    }
-    for (int j = static_cast<int>(written) + tid; j < a.c_max; j += kSelThreads) out[j] = -1;
-    if (tid == 0) a.counts[hc] = static_cast<int32_t>(written);
-}
-
 }  // namespace
 
 int select_kpt(int T) {
-    // register-resident top-k while a row fits in 32 keys per thread of 1024
-    const int per = (T + kSelThreads - 1) / kSelThreads;
-    return per <= 4 ? 4 : per <= 8 ? 8 : per <= 16 ? 16 : per <= 32 ? 32 : 0;
+    // a power of two while the digits stay in registers, whole 16-byte pieces
+    // beyond
+    const int per = static_cast<int>((static_cast<int64_t>(T) + kSelThreads - 1) / kSelThreads);
+    return per <= 8 ? 8 : per <= 16 ? 16 : per <= 32 ? 32 : (per + 7) / 8 * 8;
 }
 
 hipError_t launch_select(const SelectArgs& a, int stages, hipStream_t s) {
-    if (a.kpt != select_kpt(a.T) || a.key_stride != select_key_stride(a.T)) return hipErrorInvalidValue;
+    if (a.kpt != select_kpt(a.T) || a.digit_stride != select_digit_stride(a.T)) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     if (stages & kSelectTau) {
         if (a.mode == 0) {
             // register-resident tau cut while a row fits in 32 masses per
-            // thread of 512, then of 1024; the sweep kernel beyond
+            // thread of 512 (two workgroups on a CU), then 32 and 64 of 1024;
+            // the sweep kernel beyond (T > 65536)
             dim3 g1(a.G, a.Hkv, a.B);
             const int tper = (a.T + kTauThreads - 1) / kTauThreads;
-            const int tkpt = tper <= 8 ? 8 : tper <= 16 ? 16 : tper <= 32 ? 32 : tper <= 64 ? 64 : 0;
+            const int tkpt = tper <= 8 ? 8 : tper <= 16 ? 16 : tper <= 32 ? 32 : tper <= 64 ? 64 : tper <= 128 ? 128 : 0;
             switch (tkpt) {
                 case 8: hipLaunchKernelGGL((tau_cut_reg_kernel<8, kTauThreads>), g1, dim3(kTauThreads), 0, s, a); break;
                 case 16: hipLaunchKernelGGL((tau_cut_reg_kernel<16, kTauThreads>), g1, dim3(kTauThreads), 0, s, a); break;
                 case 32: hipLaunchKernelGGL((tau_cut_reg_kernel<32, kTauThreads>), g1, dim3(kTauThreads), 0, s, a); break;
                 case 64: hipLaunchKernelGGL((tau_cut_reg_kernel<32, kSelThreads>), g1, dim3(kSelThreads), 0, s, a); break;
+                case 128: hipLaunchKernelGGL((tau_cut_reg_kernel<64, kSelThreads>), g1, dim3(kSelThreads), 0, s, a); break;
                 default: hipLaunchKernelGGL(tau_cut_kernel, g1, dim3(kSelThreads), 0, s, a); break;
             }
         } else {
@@ -767,11 +957,10 @@ hipError_t launch_select(const SelectArgs& a, int stages, hipStream_t s) {
     if (stages & kSelectPick) {
         dim3 g3(a.Hkv, a.B);
         switch (a.kpt) {
-            case 4: hipLaunchKernelGGL(topk_reg_kernel<4>, g3, dim3(kSelThreads), 0, s, a); break;
-            case 8: hipLaunchKernelGGL(topk_reg_kernel<8>, g3, dim3(kSelThreads), 0, s, a); break;
-            case 16: hipLaunchKernelGGL(topk_reg_kernel<16>, g3, dim3(kSelThreads), 0, s, a); break;
-            case 32: hipLaunchKernelGGL(topk_reg_kernel<32>, g3, dim3(kSelThreads), 0, s, a); break;
-            default: hipLaunchKernelGGL(topk_kernel, g3, dim3(kSelThreads), 0, s, a); break;
+            case 8: hipLaunchKernelGGL(topk_kernel<8>, g3, dim3(kSelThreads), 0, s, a); break;
+            case 16: hipLaunchKernelGGL(topk_kernel<16>, g3, dim3(kSelThreads), 0, s, a); break;
+            case 32: hipLaunchKernelGGL(topk_kernel<32>, g3, dim3(kSelThreads), 0, s, a); break;
+            default: hipLaunchKernelGGL(topk_kernel<0>, g3, dim3(kSelThreads), 0, s, a); break;
         }
         e = hipGetLastError();
     }
