@@ -347,7 +347,7 @@ namespace {
 // the process ends.  In host code `scratch` names a host-side stand-in, so
 // the device address of each GPU's copy is taken once, with that GPU
 // current, and only that address is handed to the kernels.
-constexpr size_t kScratchBytes = MMSKV_NOALLOC_SCRATCH_BYTES;
+static_assert(kScratchBytes == MMSKV_NOALLOC_SCRATCH_BYTES, "the scratch that the score plan keeps to");
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;

@@ -14,6 +14,7 @@ namespace mmskv {
 // 32-row tile of each of the Gh heads per proxy block).
 constexpr int kMaxMassParts = 16;
 constexpr size_t kMaxRowLds8 = 64 * 1024;  // row normalisers (fp32) in LDS with 8-wave mass blocks
+constexpr size_t kScratchBytes = static_cast<size_t>(32) << 20;   // scratch of the allocation-free entry point, per GPU
 constexpr int kPlanCus = 256;              // CUs of the chip
 struct ScorePlan {
     int lse_waves, lse_sub, mass_waves, lse_parts, mass_parts;

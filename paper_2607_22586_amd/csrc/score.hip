@@ -1278,9 +1278,18 @@ ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units
     const int tiles = rows_pad / 32;
     ScorePlan p{};
     double best = 0.0;
+    // pass 1's partials and row normalisers take a share of the workspace
+    // that goes with the number of key blocks: where only the 8-wave blocks
+    // keep it within the scratch memory of the allocation-free entry point,
+    // they are taken (both entry points run the same plan)
+    auto lse_bytes = [&](long n) {
+        return (static_cast<size_t>(n) * rows_pad * sizeof(float2) + 255) / 256 * 256 +
+               (static_cast<size_t>(heads) * rows_pad * sizeof(float) + 255) / 256 * 256;
+    };
     for (int w = 8; w >= 4; w -= 4) {
         const int keys = w == 8 ? 1024 : 256;
         const long n = heads * ((T + keys - 1) / keys);
+        if (w == 4 && lse_bytes(n) > kScratchBytes && lse_bytes(heads * ((T + 1023) / 1024)) <= kScratchBytes) continue;
         // (with 4 rounds of workgroups, more parts no longer level the last)
         for (int r = 1; r <= kMaxLseParts && (r == 1 || (tiles / r >= 4 && n * (r - 1) < 8 * kPlanCus)); ++r) {
             const double t = plan_time(w == 8 ? kLse8 : kLse4, n * r, (tiles + r - 1) / r);
