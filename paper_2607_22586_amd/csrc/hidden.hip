@@ -14,12 +14,12 @@
 // project        q[b, h, i, :] = W_Q^(h) H~[b, i, :]: a bf16 GEMM of the
 //                (B*P) x D samples against the (Hq*d) x D weights (both with
 //                the reduction dimension contiguous) with fp32 accumulation.
-//                Without rotary tables, on full 128 x 224 tiles: four waves
-//                of 64 x 112 on v_mfma_f32_16x16x32_bf16.  Otherwise 128x128
-//                tiles of four 64x64 waves on v_mfma_f32_32x32x16_bf16, the
-//                epilogue through LDS so that the rotary pairs (e, e + d/2)
-//                of a head meet in one thread.  Both multiply by the query
-//                scale log2(e)/sqrt(d) in fp64 and round to bf16.
+//                Full tiles (of four sizes, by the matrix): four waves on
+//                v_mfma_f32_16x16x32_bf16.  Otherwise 128x128 tiles of four
+//                64x64 waves on v_mfma_f32_32x32x16_bf16.  The epilogue goes
+//                through LDS so that the rotary pairs (e, e + d/2) of a head
+//                meet in one thread; both multiply by the query scale
+//                log2(e)/sqrt(d) in fp64 and round to bf16.
 #pragma clang fp contract(off)
 
 #include <math.h>
@@ -223,6 +223,14 @@ __device__ __forceinline__ void gemm_store(const GemmStage& st, u32x4* la, u32x4
     }
 }
 
+// Rotary pair (x0, x1), scaled, as bf16 bits.
+__device__ __forceinline__ void rotate_pair(float x0, float x1, float c, float s, double scale, uint32_t& lo,
+                                            uint32_t& hi) {
+    const float a0 = x0 * c, a1 = x1 * s, b0 = x1 * c, b1 = x0 * s;
+    lo = f32_to_bf16_bits(scaled(a0 - a1, scale));
+    hi = f32_to_bf16_bits(scaled(b0 + b1, scale));
+}
+
 // Epilogue of a 128 x 128 output tile: the fp32 accumulators (wave (wm, wn)
 // holds rows wm*64.., columns wn*64..) through LDS, then the rotary pairs,
 // the softmax scale and the bf16 rounding, to the proxies' layout.
@@ -272,13 +280,9 @@ __device__ __forceinline__ void project_epilogue(const ProjectArgs& p, const flo
         } else {
             uint32_t l16[8], h16[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const float x0 = tile[r * kLd + col + q], x1 = tile[r * kLd + col + half + q];
-                const float c = p.cos[e + q], s = p.sin[e + q];
-                const float a0 = x0 * c, a1 = x1 * s, b0 = x1 * c, b1 = x0 * s;
-                l16[q] = f32_to_bf16_bits(scaled(a0 - a1, p.scale));
-                h16[q] = f32_to_bf16_bits(scaled(b0 + b1, p.scale));
-            }
+            for (int q = 0; q < 8; ++q)
+                rotate_pair(tile[r * kLd + col + q], tile[r * kLd + col + half + q], p.cos[e + q], p.sin[e + q], p.scale,
+                            l16[q], h16[q]);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 lo[q] = l16[2 * q] | (l16[2 * q + 1] << 16);
@@ -351,44 +355,45 @@ __global__ void __launch_bounds__(kGemmThreads) project_kernel(ProjectArgs p) {
     project_epilogue(p, acc, lds, m0, n0, wm, wn, lane);
 }
 
-// Full tiles with direct-to-LDS loads (global_load_lds_dwordx4): the tiles
-// of k step ks land in LDS stage ks % NS without passing through registers,
-// issued NS - 1 steps ahead; one barrier per step.  The waits are written out
-// (each wave waits for its own share of stage ks, the barrier then covers
-// every wave's share and every wave's reads of step ks - 1, whose stage the
-// step's new loads overwrite).  A row of a stage is DK / 8 chunks of 16
-// bytes, chunk c of row r at slot c ^ f(r), f chosen so that the 8 rows read
-// in one 128-byte LDS phase (one chunk each) fall in 8 different bank groups.
-template <int DK>
-struct DmaTile {
-    static constexpr int kChunks = DK / 8;                 // 16-byte chunks per row
-    static constexpr int kRow = DK * 2;                    // bytes per row
-    static constexpr int kTile = kBM * kRow;               // bytes per operand tile
-    static constexpr int kStage = 2 * kTile;               // A tile, then W tile
-    static constexpr int kRowsPerOp = 1024 / kRow;         // rows per 1 KB instruction
-    static constexpr int kOps = 32 / kRowsPerOp;           // instructions per operand per wave
-    static constexpr int kPerStage = 2 * kOps;             // loads per wave per stage
-    static __device__ __forceinline__ int slot(int r, int c) {
-        return kChunks == 4 ? c ^ ((r >> 1) & 3) : c ^ (r & 7);
-    }
+// Full TM x TN output tiles (TM = 32 AX, TN = 32 AY), four waves of 16 AX x
+// 16 AY on v_mfma_f32_16x16x32_bf16.  A k step is 64 wide and lands in one of
+// NS LDS stages by direct loads: each wave issues AX + AY of the step's loads
+// of 8 rows x 128 bytes, from a uniform base advanced per step plus
+// loop-invariant 32-bit lane offsets (chunk c of row r at slot c ^ (r & 7)).
+// A step runs its two 32-wide halves back to back: the A fragments of the
+// next half are read before a half's MFMAs, and each W fragment is refilled
+// right after the MFMAs that last read it.  The barrier sits between the
+// halves: by then every wave has its own loads of the next stage and its
+// reads of the current one complete, so after it the next stage can be read
+// and the loads NS steps ahead overwrite the current stage.
+// ROPE: columns [0, TN/2) of a tile are the lower columns of TN/2 rotary pairs
+// and the rest their partners, so that a pair meets in one row of the tile.
+constexpr int kWK = 64;
+constexpr int kWRow = kWK * 2;                      // bytes per staged row
+template <int AX, int AY, int NS>
+struct WideTile {
+    static constexpr int kM = 32 * AX, kN = 32 * AY;
+    static constexpr int kTileA = kM * kWRow;       // the A rows of a stage
+    static constexpr int kStage = (kM + kN) * kWRow;
+    // loads per wave and stage: the four waves issue the 8-row groups in
+    // turn, the A tile's 4 AX groups being loads j < AX of every wave
+    static constexpr int kLoads = AX + AY;
+    static constexpr int kLd = kN + 4;              // epilogue row pitch (floats)
+    static constexpr int kLds = NS * kStage > kM * kLd * 4 ? NS * kStage : kM * kLd * 4;
+};
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+template <int N>
+struct Tag {
+    static constexpr int value = N;
 };
 
-// wave w issues rows 32 w .. 32 w + 31 of both tiles of one step
-template <int DK>
-__device__ __forceinline__ void dma_step(const ProjectArgs& p, int m0, int n0, int k0, char* stage, int wave, int lane) {
-    using T = DmaTile<DK>;
-#pragma unroll
-    for (int op = 0; op < 2; ++op) {
-        const uint16_t* src = op == 0 ? p.a + static_cast<int64_t>(m0) * p.K : p.w + static_cast<int64_t>(n0) * p.K;
-#pragma unroll
-        for (int j = 0; j < T::kOps; ++j) {
-            const int r0 = 32 * wave + T::kRowsPerOp * j, r = r0 + lane / T::kChunks;
-            const int c = T::slot(r, lane % T::kChunks);
-            __builtin_amdgcn_global_load_lds(src + static_cast<int64_t>(r) * p.K + k0 + 8 * c,
-                                             (__attribute__((address_space(3))) void*)(stage + op * T::kTile + r0 * T::kRow),
-                                             16, 0, 0);
-        }
-    }
+__device__ __forceinline__ floatx4 mfma16(bf16x8 a, bf16x8 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// 16 bytes per lane from memory to LDS (dst + 16 * lane)
+__device__ __forceinline__ void load16_to_lds(const char* src, char* dst) {
+    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
 }
 
 // s_waitcnt with vmcnt = N and the other counters not waited on
@@ -398,196 +403,142 @@ __device__ __forceinline__ void wait_vm() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-template <int DK, int NS>
-__global__ void __launch_bounds__(kGemmThreads) project_dma_kernel(ProjectArgs p) {
-    using T = DmaTile<DK>;
-    static_assert(kBM == kBN && kBM == 128, "four waves of 32 rows per operand");
-    // the stages, or the epilogue's fp32 tile if that is larger
-    constexpr int kBytes = NS * T::kStage > kBM * (kBN + 4) * 4 ? NS * T::kStage : kBM * (kBN + 4) * 4;
-    __shared__ u32x4 lds[kBytes / 16];
-    char* base = reinterpret_cast<char*>(lds);
-    const int m0 = static_cast<int>(blockIdx.x) * kBM, n0 = static_cast<int>(blockIdx.y) * kBN;
-    const int wave = static_cast<int>(threadIdx.x) / kWave, lane = lane_id();
-    const int wm = wave >> 1, wn = wave & 1;
-    const int n_k = p.K / DK;
-    floatx16 acc[2][2];
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[x][y][i] = 0.f;
-#pragma unroll
-    for (int st = 0; st < NS - 1; ++st)
-        if (st < n_k) dma_step<DK>(p, m0, n0, st * DK, base + st * T::kStage, wave, lane);
-    for (int ks = 0; ks < n_k; ++ks) {
-        // this wave's loads of stage ks are the oldest outstanding; later
-        // stages in flight: min(NS - 2, n_k - 1 - ks)
-        const int later = min(NS - 2, n_k - 1 - ks);
-        if (later >= 3) wait_vm<3 * T::kPerStage>();
-        else if (later == 2) wait_vm<2 * T::kPerStage>();
-        else if (later == 1) wait_vm<T::kPerStage>();
-        else wait_vm<0>();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (ks + NS - 1 < n_k)
-            dma_step<DK>(p, m0, n0, (ks + NS - 1) * DK, base + ((ks + NS - 1) % NS) * T::kStage, wave, lane);
-        const char* sa = base + (ks % NS) * T::kStage;
-        const char* sw = sa + T::kTile;
-        // fragments of k chunk kc + 1 are read while the MFMAs of kc run
-        bf16x8 fa[2][2], fw[2][2];
-        auto read_frags = [&](int kc, int buf) {
-            const int c = 2 * kc + (lane >> 5);
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const int ra = wm * 64 + 32 * x + (lane & 31), rw = wn * 64 + 32 * x + (lane & 31);
-                fa[buf][x] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(sa + ra * T::kRow + 16 * T::slot(ra, c)));
-                fw[buf][x] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(sw + rw * T::kRow + 16 * T::slot(rw, c)));
-            }
-        };
-        read_frags(0, 0);
-#pragma unroll
-        for (int kc = 0; kc < DK / 16; ++kc) {
-            if (kc + 1 < DK / 16) read_frags(kc + 1, (kc + 1) & 1);
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y) acc[x][y] = mfma32(fa[kc & 1][x], fw[kc & 1][y], acc[x][y]);
-        }
-    }
-    // every wave's reads done before the tile reuses the stages
-    asm volatile("" ::: "memory");
-    __syncthreads();
-    project_epilogue(p, acc, lds, m0, n0, wm, wn, lane);
+// s_waitcnt vmcnt(N) lgkmcnt(0)
+template <int N>
+__device__ __forceinline__ void wait_vm_lgkm0() {
+    static_assert(N < 64, "vmcnt field");
+    __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
 }
 
-// Full tiles without rotary tables: 128 x 224 output tiles (the benchmark
-// shape has 16 x 16 of them, one per CU), four waves of 64 x 112 on
-// v_mfma_f32_16x16x32_bf16 (4 x 7 accumulator blocks per wave).  A k step is
-// 64 wide and lands in one of two LDS stages by direct loads: each wave issues
-// 11 of the step's 44 loads of 8 rows x 128 bytes, from a uniform base
-// advanced per step plus loop-invariant 32-bit lane offsets (chunk c of row r
-// at slot c ^ (r & 7)).  A step runs its two 32-wide halves back to back: the
-// A fragments of the next half are read before a half's 28 MFMAs, and each W
-// fragment is refilled right after the four MFMAs that last read it.  The
-// barrier sits between the halves: by then every wave has its own loads of
-// the next stage and its reads of the current one complete, so after it the
-// next stage can be read and the loads two steps ahead overwrite the current
-// stage.
-constexpr int kWM = 128, kWN = 224, kWK = 64;
-constexpr int kWRow = kWK * 2;                      // bytes per staged row
-constexpr int kWTileA = kWM * kWRow;                // the A rows of a stage
-constexpr int kWStage = (kWM + kWN) * kWRow;        // 45,056 bytes
-constexpr int kWLoads = (kWM + kWN) / 8 / 4;        // loads per wave and stage
-constexpr int kWLd = kWN + 4;                       // epilogue row pitch (floats)
-constexpr int kWLds = 2 * kWStage > kWM * kWLd * 4 ? 2 * kWStage : kWM * kWLd * 4;
-// the four waves issue the 8-row groups of a stage in turn: the A tile's 16
-// groups are loads j < 4 of every wave, the W tile's 28 the rest
-static_assert((kWM + kWN) % 32 == 0 && kWM / 8 == 4 * 4 && kGemmThreads == 4 * kWave, "load split");
-static_assert(kWN == 2 * 112 && kWM == 2 * 64, "four waves of 64 x 112");
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-// s_waitcnt vmcnt(0) lgkmcnt(0)
-__device__ __forceinline__ void wait_vm_lgkm0() { __builtin_amdgcn_s_waitcnt(0x0070); }
-
+template <int AX, int AY, int NS, bool ROPE>
 __global__ void __launch_bounds__(kGemmThreads) project_wide_kernel(ProjectArgs p) {
-    __shared__ u32x4 lds[kWLds / 16];
+    using T = WideTile<AX, AY, NS>;
+    static_assert(NS >= 2 && NS <= 4, "the waits count up to two later stages");
+    __shared__ u32x4 lds[T::kLds / 16];
     char* base = reinterpret_cast<char*>(lds);
-    const int nN = p.N / kWN;
-    const int m0 = static_cast<int>(blockIdx.x) / nN * kWM, n0 = static_cast<int>(blockIdx.x) % nN * kWN;
+    const int half = p.d / 2;
+    const int nN = p.N / T::kN;
+    const int m0 = static_cast<int>(blockIdx.x) / nN * T::kM, n0 = static_cast<int>(blockIdx.x) % nN * T::kN;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave), lane = lane_id();
     const int wm = wave >> 1, wn = wave & 1;
-    const int n_k = p.K / kWK;                      // at least 2 (checked by the host)
-    floatx4 acc[4][7];
+    const int n_k = p.K / kWK;                      // at least NS (checked by the host)
+    floatx4 acc[AX][AY];
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int x = 0; x < AX; ++x)
 #pragma unroll
-        for (int y = 0; y < 7; ++y) acc[x][y] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int y = 0; y < AY; ++y) acc[x][y] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // load j of a stage: rows 8 (wave + 4 j) .. + 7 of the A tile (j < 4) or
-    // of the W tile (j >= 4, less 16 groups); lane -> row + (lane >> 3), slot lane & 7
-    uint32_t voff[kWLoads];
+    // load j of a stage: rows 8 (wave + 4 j) .. + 7 of the A tile (j < AX) or
+    // of the W tile (j >= AX, less 4 AX groups); lane -> row + (lane >> 3),
+    // slot lane & 7; offsets from the tile's first row (m0, w0)
+    const int w0 = ROPE ? n0 / 2 / half * p.d + n0 / 2 % half : n0;
+    uint32_t voff[T::kLoads];
 #pragma unroll
-    for (int j = 0; j < kWLoads; ++j) {
-        const int g = wave + 4 * j - (j < 4 ? 0 : kWM / 8);
+    for (int j = 0; j < T::kLoads; ++j) {
+        const int g = wave + 4 * j - (j < AX ? 0 : 4 * AX);
         const int r = 8 * g + (lane >> 3);
-        voff[j] = static_cast<uint32_t>(((j < 4 ? m0 : n0) + r) * p.K * 2 + 16 * ((lane & 7) ^ (r & 7)));
+        int row = r;
+        if (ROPE && j >= AX) {
+            // rotary pair n0 / 2 + r % (TN / 2): its lower column, or its upper one
+            const int hi = r >= T::kN / 2 ? 1 : 0, pr = n0 / 2 + r - hi * (T::kN / 2);
+            row = pr / half * p.d + pr % half + hi * half - w0;
+        }
+        voff[j] = static_cast<uint32_t>(row * p.K * 2 + 16 * ((lane & 7) ^ (r & 7)));
     }
+    const char* a0 = reinterpret_cast<const char*>(p.a + static_cast<int64_t>(m0) * p.K);
+    const char* wr0 = reinterpret_cast<const char*>(p.w + static_cast<int64_t>(w0) * p.K);
     auto loads = [&](int k0, char* stage) {
-        const char* ab = reinterpret_cast<const char*>(p.a) + 2 * k0;
-        const char* wb = reinterpret_cast<const char*>(p.w) + 2 * k0;
+        const char* ab = a0 + 2 * k0;
+        const char* wb = wr0 + 2 * k0;
 #pragma unroll
-        for (int j = 0; j < kWLoads; ++j) {
-            const int g = wave + 4 * j - (j < 4 ? 0 : kWM / 8);
-            char* dst = stage + (j < 4 ? 0 : kWTileA) + 8 * g * kWRow;
-            __builtin_amdgcn_global_load_lds((j < 4 ? ab : wb) + voff[j],
-                                             (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+        for (int j = 0; j < T::kLoads; ++j) {
+            const int g = wave + 4 * j - (j < AX ? 0 : 4 * AX);
+            char* dst = stage + (j < AX ? 0 : T::kTileA) + 8 * g * kWRow;
+            load16_to_lds((j < AX ? ab : wb) + voff[j], dst);
         }
     };
-    // fragment rows wm*64 + 16x + (lane & 15) and wn*112 + 16y + (lane & 15)
+    // fragment rows wm*16*AX + 16x + (lane & 15) and wn*16*AY + 16y + (lane & 15)
     // (both = lane & 7 mod 8), 16-byte chunk 4 h + (lane >> 4) of half h
-    const int rA = wm * 64 + (lane & 15), rW = wn * 112 + (lane & 15);
+    const int rA = wm * 16 * AX + (lane & 15), rW = wn * 16 * AY + (lane & 15);
     const int oA0 = rA * kWRow + 16 * ((lane >> 4) ^ (lane & 7));
     const int oA1 = rA * kWRow + 16 * ((4 + (lane >> 4)) ^ (lane & 7));
-    const int oW0 = kWTileA + rW * kWRow + 16 * ((lane >> 4) ^ (lane & 7));
-    const int oW1 = kWTileA + rW * kWRow + 16 * ((4 + (lane >> 4)) ^ (lane & 7));
+    const int oW0 = T::kTileA + rW * kWRow + 16 * ((lane >> 4) ^ (lane & 7));
+    const int oW1 = T::kTileA + rW * kWRow + 16 * ((4 + (lane >> 4)) ^ (lane & 7));
     auto rd = [&](const char* q) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(q)); };
-    bf16x8 fa0[4], fa1[4], fw[7];
+    bf16x8 fa0[AX], fa1[AX], fw[AY];
 
-    loads(0, base);
-    loads(kWK, base + kWStage);
-    wait_vm<kWLoads>();
+#pragma unroll
+    for (int st = 0; st < NS; ++st) loads(st * kWK, base + st * T::kStage);
+    wait_vm<(NS - 1) * T::kLoads>();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
-    for (int x = 0; x < 4; ++x) fa0[x] = rd(base + oA0 + x * 16 * kWRow);
+    for (int x = 0; x < AX; ++x) fa0[x] = rd(base + oA0 + x * 16 * kWRow);
 #pragma unroll
-    for (int y = 0; y < 7; ++y) fw[y] = rd(base + oW0 + y * 16 * kWRow);
+    for (int y = 0; y < AY; ++y) fw[y] = rd(base + oW0 + y * 16 * kWRow);
 
     // step ks on stage st (half 0's fragments already in fa0 / fw); nst is
-    // the next stage; the loads of step ks + 2 go to st
-    auto step = [&](int ks, char* st, const char* nst, auto last_tag) {
-        constexpr bool kLast = decltype(last_tag)::value;
+    // the next stage; the loads of step ks + NS go to st.  LATER: stages in
+    // flight after stage ks + 1 (min(NS - 2, n_k - 2 - ks)); -1: the last step
+    auto step = [&](int ks, char* st, const char* nst, auto later_tag) {
+        constexpr int kLater = decltype(later_tag)::value;
+        constexpr bool kLast = kLater < 0;
 #pragma unroll
-        for (int x = 0; x < 4; ++x) fa1[x] = rd(st + oA1 + x * 16 * kWRow);
+        for (int x = 0; x < AX; ++x) fa1[x] = rd(st + oA1 + x * 16 * kWRow);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int y = 0; y < 7; ++y) {
+        for (int y = 0; y < AY; ++y) {
 #pragma unroll
-            for (int x = 0; x < 4; ++x) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa0[x], fw[y], acc[x][y], 0, 0, 0);
+            for (int x = 0; x < AX; ++x) acc[x][y] = mfma16(fa0[x], fw[y], acc[x][y]);
             fw[y] = rd(st + oW1 + y * 16 * kWRow);
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (!kLast) {
-            wait_vm_lgkm0();
+            wait_vm_lgkm0<(kLast ? 0 : kLater) * T::kLoads>();
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            if (ks + 2 < n_k) loads((ks + 2) * kWK, st);
+            if (ks + NS < n_k) loads((ks + NS) * kWK, st);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) fa0[x] = rd(nst + oA0 + x * 16 * kWRow);
+            for (int x = 0; x < AX; ++x) fa0[x] = rd(nst + oA0 + x * 16 * kWRow);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int y = 0; y < 7; ++y) {
+        for (int y = 0; y < AY; ++y) {
 #pragma unroll
-            for (int x = 0; x < 4; ++x) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1[x], fw[y], acc[x][y], 0, 0, 0);
+            for (int x = 0; x < AX; ++x) acc[x][y] = mfma16(fa1[x], fw[y], acc[x][y]);
             if constexpr (!kLast) fw[y] = rd(nst + oW0 + y * 16 * kWRow);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     int ks = 0;
-    for (; ks + 2 < n_k; ks += 2) {
-        step(ks, base, base + kWStage, std::false_type{});
-        step(ks + 1, base + kWStage, base, std::false_type{});
+    if constexpr (NS == 2) {
+        for (; ks + 2 < n_k; ks += 2) {
+            step(ks, base, base + T::kStage, Tag<0>{});
+            step(ks + 1, base + T::kStage, base, Tag<0>{});
+        }
+        if (ks + 1 < n_k) {
+            step(ks, base, base + T::kStage, Tag<0>{});
+            ++ks;
+        }
+        step(ks, base + (ks & 1) * T::kStage, nullptr, Tag<-1>{});
+    } else {
+        int s0 = 0, s1 = 1;                         // stages of steps ks and ks + 1
+        auto next = [&]() {
+            ++ks;
+            s0 = s1;
+            s1 = s1 + 1 == NS ? 0 : s1 + 1;
+        };
+        for (; ks + NS <= n_k; next()) step(ks, base + s0 * T::kStage, base + s1 * T::kStage, Tag<NS - 2>{});
+        if constexpr (NS == 4) {
+            step(ks, base + s0 * T::kStage, base + s1 * T::kStage, Tag<1>{});
+            next();
+        }
+        step(ks, base + s0 * T::kStage, base + s1 * T::kStage, Tag<0>{});
+        next();
+        step(ks, base + s0 * T::kStage, nullptr, Tag<-1>{});
     }
-    if (ks + 1 < n_k) {
-        step(ks, base, base + kWStage, std::false_type{});
-        ++ks;
-    }
-    step(ks, base + (ks & 1) * kWStage, nullptr, std::true_type{});
 
     // epilogue: the fp32 tile through LDS (every wave's stage reads are done),
     // then 8 consecutive columns of one row per thread and group: the query
@@ -596,19 +547,44 @@ __global__ void __launch_bounds__(kGemmThreads) project_wide_kernel(ProjectArgs 
     __syncthreads();
     float* tile = reinterpret_cast<float*>(lds);
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int x = 0; x < AX; ++x)
 #pragma unroll
-        for (int y = 0; y < 7; ++y)
+        for (int y = 0; y < AY; ++y)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                tile[(wm * 64 + 16 * x + 4 * (lane >> 4) + i) * kWLd + wn * 112 + 16 * y + (lane & 15)] = acc[x][y][i];
+                tile[(wm * 16 * AX + 16 * x + 4 * (lane >> 4) + i) * T::kLd + wn * 16 * AY + 16 * y + (lane & 15)] = acc[x][y][i];
     __syncthreads();
-    constexpr int kGroups = kWN / 8;
-    for (int g = static_cast<int>(threadIdx.x); g < kWM * kGroups; g += kGemmThreads) {
+    if constexpr (ROPE) {
+        // columns c .. c + 7 of a row with their partners TN / 2 columns on:
+        // the same head's lower and upper half
+        constexpr int kPairs = T::kN / 16;
+        for (int g = static_cast<int>(threadIdx.x); g < T::kM * kPairs; g += kGemmThreads) {
+            const int r = g / kPairs, c = 8 * (g % kPairs);
+            const int m = m0 + r, pr = n0 / 2 + c;
+            const int bb = m / p.P, i = m % p.P, h = pr / half, e = pr % half;
+            const float* src = tile + r * T::kLd + c;
+            uint32_t l16[8], h16[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                rotate_pair(src[q], src[T::kN / 2 + q], p.cos[e + q], p.sin[e + q], p.scale, l16[q], h16[q]);
+            u32x4 lo, hi;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                lo[q] = l16[2 * q] | (l16[2 * q + 1] << 16);
+                hi[q] = h16[2 * q] | (h16[2 * q + 1] << 16);
+            }
+            uint16_t* out = p.out + ((static_cast<int64_t>(bb) * p.Hq + h) * p.P + i) * p.d + e;
+            *reinterpret_cast<u32x4*>(out) = lo;
+            *reinterpret_cast<u32x4*>(out + half) = hi;
+        }
+        return;
+    }
+    constexpr int kGroups = T::kN / 8;
+    for (int g = static_cast<int>(threadIdx.x); g < T::kM * kGroups; g += kGemmThreads) {
         const int r = g / kGroups, c = 8 * (g % kGroups);
         const int m = m0 + r, n = n0 + c;
         const int bb = m / p.P, i = m % p.P, h = n / p.d, e = n % p.d;
-        const float* src = tile + r * kWLd + c;
+        const float* src = tile + r * T::kLd + c;
         u32x4 v;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -616,6 +592,24 @@ __global__ void __launch_bounds__(kGemmThreads) project_wide_kernel(ProjectArgs 
         *reinterpret_cast<u32x4*>(p.out + ((static_cast<int64_t>(bb) * p.Hq + h) * p.P + i) * p.d + e) = v;
     }
 }
+
+template <int AX, int AY, int NS>
+hipError_t launch_wide(const ProjectArgs& p, hipStream_t s) {
+    using T = WideTile<AX, AY, NS>;
+    const dim3 g((p.M / T::kM) * (p.N / T::kN));
+    if (p.cos == nullptr) hipLaunchKernelGGL((project_wide_kernel<AX, AY, NS, false>), g, dim3(kGemmThreads), 0, s, p);
+    else hipLaunchKernelGGL((project_wide_kernel<AX, AY, NS, true>), g, dim3(kGemmThreads), 0, s, p);
+    return hipGetLastError();
+}
+
+// Tile sizes and the measured time of one k step of a round of workgroups
+// (one per CU), in units of 10 ns: the loads, their wait and the barrier do not
+// shrink with the tile, so a tile is only worth its size while the grid fills
+// the CUs.
+struct WideForm {
+    int m, n, stages, cost;
+};
+constexpr WideForm kWide[] = {{128, 224, 2, 104}, {128, 128, 3, 68}, {64, 128, 4, 44}, {64, 64, 3, 33}};
 
 }  // namespace
 
@@ -637,21 +631,35 @@ hipError_t launch_hidden_proxies(const HiddenArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_project(const ProjectArgs& p, hipStream_t s) {
-    // without rotary tables, on full 128 x 224 tiles whose lane offsets fit
-    // in 31 bits: one 128 x 224 tile per workgroup
-    if (p.cos == nullptr && p.M % kWM == 0 && p.N % kWN == 0 && p.K % kWK == 0 && p.K >= 2 * kWK &&
-        static_cast<int64_t>(p.M > p.N ? p.M : p.N) * p.K * 2 < (static_cast<int64_t>(1) << 31)) {
-        hipLaunchKernelGGL(project_wide_kernel, dim3((p.M / kWM) * (p.N / kWN)), dim3(kGemmThreads), 0, s, p);
-        return hipGetLastError();
+    // the tile size with the smallest modelled time, among those that divide
+    // the matrix and whose stages a reduction of K fills.  Measured (us), the
+    // 128 x 128 tiles in two stages that all but the 128 x 224 ones replace
+    // against the choice made here, M x N = K: 512 x 3584 47 -> 25, 1024 x
+    // 3584 49 -> 38, 2048 x 3584 with rotary tables 68 -> 57, 512 x 2048 24 ->
+    // 10.7, 1024 x 2048 25.6 -> 14.5, 2048 x 2048 27.5 -> 22.6.
+    int best = -1;
+    int64_t best_cost = 0;
+    if (p.K % kWK == 0 && p.K <= (1 << 20)) {          // (lane offsets within 32 bits)
+        for (int i = 0; i < 4; ++i) {
+            const WideForm& f = kWide[i];
+            if (p.M % f.m != 0 || p.N % f.n != 0 || p.K < f.stages * kWK) continue;
+            const int64_t tiles = static_cast<int64_t>(p.M / f.m) * (p.N / f.n);
+            const int64_t cost = (tiles + kPlanCus - 1) / kPlanCus * f.cost;
+            if (best < 0 || cost < best_cost) {
+                best = i;
+                best_cost = cost;
+            }
+        }
+    }
+    switch (best) {
+        case 0: return launch_wide<4, 7, 2>(p, s);
+        case 1: return launch_wide<4, 4, 3>(p, s);
+        case 2: return launch_wide<2, 4, 4>(p, s);
+        case 3: return launch_wide<2, 2, 3>(p, s);
+        default: break;
     }
     dim3 g((p.M + kBM - 1) / kBM, (p.N + kBN - 1) / kBN);
-    // full tiles: 64-wide k steps in two LDS stages loaded directly (two
-    // workgroups per CU; deeper rings of 32- or 64-wide steps leave one per
-    // CU, or more barriers per MFMA, and measured slower)
-    if (p.M % kBM == 0 && p.N % kBN == 0 && p.K % 64 == 0)
-        hipLaunchKernelGGL((project_dma_kernel<64, 2>), g, dim3(kGemmThreads), 0, s, p);
-    else
-        hipLaunchKernelGGL(project_kernel, g, dim3(kGemmThreads), 0, s, p);
+    hipLaunchKernelGGL(project_kernel, g, dim3(kGemmThreads), 0, s, p);
     return hipGetLastError();
 }
 

@@ -124,7 +124,17 @@ def test_hidden_proxies_bit_exact(B, P, D, gamma, layer):
     (2, 64, 3584, 28, 128, False), (3, 40, 200, 3, 64, False), (1, 50, 136, 2, 128, True),
     (2, 33, 3584, 4, 64, True), (1, 1, 8, 1, 64, False),
     # full 128 x 224 tiles without rotation, 2, 3 and 5 k steps of 64
-    (2, 128, 128, 7, 64, False), (1, 128, 192, 14, 64, False), (1, 256, 320, 7, 64, False)])
+    (2, 128, 128, 7, 64, False), (1, 128, 192, 14, 64, False), (1, 256, 320, 7, 64, False),
+    # the same with rotation: the pairs of a tile are not whole heads
+    (2, 128, 128, 7, 64, True), (1, 128, 192, 14, 64, True), (1, 256, 128, 7, 128, True),
+    # and at 3 and 5 k steps, 4 rounds of the smallest tiles
+    (7, 1024, 192, 7, 64, False), (7, 1024, 320, 7, 64, True),
+    # 64 x 64 tiles (3 stages): their least reduction, one step more, one batch row of 512
+    (1, 64, 192, 1, 64, False), (2, 64, 256, 3, 64, True), (1, 512, 192, 1, 128, True), (1, 512, 448, 4, 128, False),
+    # 64 x 128 tiles (4 stages): 3 x 88 = 264 tiles of 64 x 64, at 4, 5 and 6 steps
+    (1, 192, 256, 88, 64, True), (1, 192, 320, 44, 128, False), (3, 64, 384, 44, 128, True),
+    # 128 x 128 tiles (3 stages): 5 x 32 tiles, 320 of 64 x 128
+    (5, 128, 192, 32, 128, True), (1, 640, 256, 64, 64, False), (5, 128, 320, 32, 128, False)])
 def test_projection_within_bound(B, P, D, Hq, d, rope):
     rng_in = wl.custom_hidden(B, P, D, Hq, d, seed=B * 1000 + P)
     hp = rng_in["hidden"]                        # any bf16 [B, P, D] serves as samples
