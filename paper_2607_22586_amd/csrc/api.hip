@@ -2,6 +2,7 @@
 // launches.  Every check runs on the host before anything is enqueued.
 #include <math.h>
 #include <stdint.h>
+#include <string.h>
 
 #include <atomic>
 #include <mutex>
@@ -547,18 +548,11 @@ int check_decode(const mmskv_shape* shape, int32_t n_dec) {
     return MMSKV_OK;
 }
 
-// partials, then the scaled decode queries
-size_t decode_part_bytes(const mmskv_shape* shape, int32_t n_dec) {
+// the coverage partials
+size_t decode_ws(const mmskv_shape* shape, int32_t n_dec) {
     const int64_t Gh = shape->Hq / shape->Hkv;
     return align_up(static_cast<size_t>(shape->B) * shape->Hkv * decode_key_blocks(shape->T) *
                     decode_rows_pad(static_cast<int>(Gh), n_dec) * sizeof(float4));
-}
-
-size_t decode_ws(const mmskv_shape* shape, int32_t n_dec) {
-    const int64_t Gh = shape->Hq / shape->Hkv;
-    return decode_part_bytes(shape, n_dec) +
-           align_up(static_cast<size_t>(shape->B) * shape->Hkv * decode_rows_pad(static_cast<int>(Gh), n_dec) *
-                    shape->d * sizeof(uint16_t));
 }
 
 }  // namespace
@@ -610,10 +604,17 @@ int mmshiftkv_decode_check(const mmskv_shape* shape, int32_t n_dec, const uint16
     a.rows = a.Gh * n_dec;
     a.rows_pad = decode_rows_pad(a.Gh, n_dec);
     a.n_kb = decode_key_blocks(shape->T);
-    a.scale = query_scale(shape->d);
+    {
+        const double scale = query_scale(shape->d);
+        const float full = static_cast<float>(scale);
+        uint32_t bits;
+        memcpy(&bits, &full, sizeof bits);
+        bits &= 0xFFFFFF00u;                           // 16 significant bits, rounded down
+        memcpy(&a.scale_hi, &bits, sizeof bits);
+        a.scale_lo = static_cast<float>(scale - static_cast<double>(a.scale_hi));
+    }
     a.lane_sum_hi = lane_sum_limit(shape->T, 32);
     a.part = static_cast<float4*>(workspace);
-    a.qsc = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + decode_part_bytes(shape, n_dec));
     a.coverage = coverage;
     a.out = out;
     return status_of(launch_decode_check(a, static_cast<hipStream_t>(stream)));

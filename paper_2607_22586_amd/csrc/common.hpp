@@ -17,6 +17,15 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float x) {
     return (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
 }
 
+// bf16 bit patterns of two fp32 values, packed (lo, hi), by one conversion
+// instruction: the same bits as f32_to_bf16_bits for every finite value (all
+// of them compared on the card, subnormal ones too).
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{lo, hi}), bf16x2));
+}
+
 // Eight consecutive bf16 values (16 bytes) as an MFMA operand.
 __device__ __forceinline__ bf16x8 load_bf16x8(const uint16_t* p) {
     u32x4 v = *reinterpret_cast<const u32x4*>(p);

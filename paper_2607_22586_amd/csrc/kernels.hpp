@@ -127,10 +127,9 @@ struct DecodeArgs {
     int rows;                  // Gh * n_dec decode queries per KV head
     int rows_pad;              // rows rounded up to 32
     int n_kb;                  // key blocks
-    double scale;              // log2(e) / sqrt(d), applied to the queries
+    float scale_hi, scale_lo;  // log2(e) / sqrt(d), applied to the queries, as the sum of its upper 16 significant bits and the rest
     float lane_sum_hi;         // block sums from zero while every lane sum is below this
     float4* part;              // [B, Hkv, n_kb, rows_pad] (max, sum all, sum kept), base 2
-    uint16_t* qsc;             // [B, Hkv, rows_pad, d] scaled decode queries (bf16)
     float* coverage;           // [B, Hq, n_dec]
     float* out;                // [B, Hq, n_dec, d]
 };

@@ -86,14 +86,32 @@ def test_decode_check_keep_all_ragged():
 
 
 def test_decode_check_fp32_cache():
-    """fp32 K/V (the compacted cache keeps fp32, so decode attention takes the
-    fp32 VALU kernel; coverage scores bf16-rounded keys as the prefill does):
+    """fp32 K/V (the compacted cache keeps fp32, so decode attention takes
+    fp32 products; coverage scores bf16-rounded keys as the prefill does):
     T = 700, d = 64, budget 300 (two chunks of cached keys), 6 decode queries."""
     x = wl.custom_layer(1, 4, 2, 700, 4, 64, dtype="fp32", seed=11)
     x["q_dec"] = (2.0 * torch.randn((1, 4, 6, 64), generator=torch.Generator().manual_seed(13))).to(torch.bfloat16)
     cfg = bd.SelectionConfig(P=64, G=4, seed=5)
     g = gpu_check(x, cfg, budget=300)
     assert g[4].dtype == np.float32
+    compare(x, g)
+
+
+# B, Hq, Hkv, T, d, dtype, decode queries, budget: one key and one query; fewer
+# keys than a wave's 64; exactly one chunk of 256 kept keys and one more; 33 and
+# 256 rows of a KV head (a second row tile, the most); 65 and 129 key blocks
+# (a second and a third round of the coverage merge)
+@pytest.mark.parametrize("B,Hq,Hkv,T,d,dtype,n_dec,budget", [
+    (1, 1, 1, 1, 64, "bf16", 1, 1), (2, 2, 1, 1, 128, "fp32", 1, 4), (1, 4, 2, 50, 128, "bf16", 3, 20),
+    (1, 4, 2, 50, 64, "fp32", 3, 20), (2, 4, 2, 600, 128, "fp32", 4, 256), (1, 4, 2, 600, 128, "fp32", 4, 257),
+    (1, 4, 2, 600, 64, "bf16", 4, 257), (1, 33, 1, 300, 128, "fp32", 1, 100), (1, 11, 1, 300, 64, "bf16", 3, 100),
+    (1, 16, 1, 513, 128, "bf16", 16, 200), (1, 16, 1, 513, 64, "fp32", 16, 513),
+    (1, 2, 1, 65 * 256 - 3, 64, "bf16", 2, 40), (1, 2, 1, 128 * 256 + 1, 64, "fp32", 2, 40)])
+def test_decode_check_edges(B, Hq, Hkv, T, d, dtype, n_dec, budget):
+    x = wl.custom_layer(B, Hq, Hkv, T, 4, d, dtype=dtype, seed=T + d)
+    gen = torch.Generator().manual_seed(T)
+    x["q_dec"] = (2.0 * torch.randn((B, Hq, n_dec, d), generator=gen)).to(torch.bfloat16)
+    g = gpu_check(x, bd.SelectionConfig(P=64, G=4, seed=7), budget)
     compare(x, g)
 
 
