@@ -41,12 +41,16 @@ __global__ void __launch_bounds__(kProxyThreads) build_proxies_kernel(ProxyArgs 
     const int h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     const int64_t qbase = static_cast<int64_t>(b) * a.qsb + static_cast<int64_t>(h) * a.qsh;
 
-    // Workgroup x owns quads [x*qpb, (x+1)*qpb) of every proxy of the head
-    // (with rotary placement also their partner quads d/8 further on), so it
-    // needs the statistics of kBlockDims = 16 dimensions only.
+    // Workgroup x, part y of it, owns quads [x*qpb, (x+1)*qpb) of the part's
+    // proxies of the head (with rotary placement also their partner quads d/8
+    // further on), so it needs the statistics of kBlockDims = 16 dimensions
+    // only.
     const bool rope = a.cos_f != nullptr;
-    const int qpb = rope ? kBlockDims / 8 : kBlockDims / 4;
-    const int q0 = blockIdx.x * qpb;
+    const int qsh = rope ? 1 : 2, qpb = 1 << qsh;
+    static_assert(kBlockDims / 8 == 2 && kBlockDims / 4 == 4, "quads per workgroup");
+    const int n_blocks = d / kBlockDims;
+    const int part = static_cast<int>(blockIdx.x) / n_blocks, q0 = (static_cast<int>(blockIdx.x) % n_blocks) * qpb;
+    const int parts = static_cast<int>(gridDim.x) / n_blocks;
     auto dim_of = [&](int slot) {
         return rope ? (slot < kBlockDims / 2 ? 4 * q0 + slot : half + 4 * q0 + slot - kBlockDims / 2) : 4 * q0 + slot;
     };
@@ -57,30 +61,76 @@ __global__ void __launch_bounds__(kProxyThreads) build_proxies_kernel(ProxyArgs 
             win[e] = static_cast<float>(load_q(a, qbase + static_cast<int64_t>(w0 + w) * a.qst + dim_of(slot)));
         }
     };
+    // the draws of proxy i, quad jq, and with rotary placement of its partner
+    // quad (the draws are fp32 values: keeping them as fp32 and widening later
+    // is exact)
+    auto draw = [&](int item, float (&z1)[4], float (&z2)[4]) {
+        const int i = item >> qsh, jq = q0 + (item & (qpb - 1));
+        double z[4];
+        normal_quad(a.key0, a.key1, b, a.layer, h, i, jq, z);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z1[e] = static_cast<float>(z[e]);
+        if (rope) normal_quad(a.key0, a.key1, b, a.layer, h, i, jq + d / 8, z);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z2[e] = rope ? static_cast<float>(z[e]) : 0.f;
+    };
+    const int n_items = static_cast<int>(static_cast<int64_t>(a.P) * (part + 1) / parts) << qsh;
+    const int first = (static_cast<int>(static_cast<int64_t>(a.P) * part / parts) << qsh) + tid;
+    // A window of up to kWinChunk rows is fetched by one round of loads (each
+    // thread's at once), and this thread's first kPreItems items are drawn
+    // before the statistics are published: every wave draws while the
+    // statistics lanes run their serial sums.
+    constexpr int kPreItems = 4;
+    constexpr int kStagePer = kWinChunk * kBlockDims / kProxyThreads;
+    const bool one_chunk = a.W <= kWinChunk;
+    float zp[kPreItems][4], zp2[kPreItems][4];
+    // element e of the window chunk: thread e % 256, load e / 256
+    auto row_of = [&](int k) { return (tid + k * kProxyThreads) / kBlockDims; };
+    if (one_chunk) {
+        float sv[kStagePer];
+        auto fetch = [&](auto* q) {
+            const int64_t col = qbase + dim_of(tid % kBlockDims);
+#pragma unroll
+            for (int k = 0; k < kStagePer; ++k) {
+                const auto x = q[col + static_cast<int64_t>(min(row_of(k), a.W - 1)) * a.qst];
+                if constexpr (sizeof(x) == 4) sv[k] = x;
+                else sv[k] = __uint_as_float(static_cast<uint32_t>(x) << 16);
+            }
+        };
+        if (a.q_dtype == 0) fetch(static_cast<const float*>(a.q));
+        else fetch(static_cast<const uint16_t*>(a.q));
+#pragma unroll
+        for (int k = 0; k < kStagePer; ++k)
+            if (row_of(k) < a.W) win[tid + k * kProxyThreads] = sv[k];
+        __syncthreads();
+    }
     // mean, then (population or sample) variance, summed in window order;
-    // thread `slot` < kBlockDims owns one dimension
+    // thread `slot` < kBlockDims owns one dimension.  f(value) for the n
+    // staged rows, kStatBatch of them per LDS round trip
     const bool owner = tid < kBlockDims;
+    auto each_row = [&](int n, auto&& f) {
+        int w = 0;
+        for (; w + kStatBatch <= n; w += kStatBatch) {
+            float v[kStatBatch];
+#pragma unroll
+            for (int k = 0; k < kStatBatch; ++k) v[k] = win[(w + k) * kBlockDims + tid];
+#pragma unroll
+            for (int k = 0; k < kStatBatch; ++k) f(static_cast<double>(v[k]));
+        }
+        for (; w < n; ++w) f(static_cast<double>(win[w * kBlockDims + tid]));
+    };
     double acc = 0.0;
     for (int w0 = 0; w0 < a.W; w0 += kWinChunk) {
         const int n = min(kWinChunk, a.W - w0);
-        __syncthreads();
-        stage(w0, n);
-        __syncthreads();
-        if (owner) {
-            // LDS reads kStatBatch rows at a time, so one read latency covers a batch
-            for (int w0b = 0; w0b < n; w0b += kStatBatch) {
-                float v[kStatBatch];
-#pragma unroll
-                for (int k = 0; k < kStatBatch; ++k) v[k] = w0b + k < n ? win[(w0b + k) * kBlockDims + tid] : 0.f;
-#pragma unroll
-                for (int k = 0; k < kStatBatch; ++k)
-                    if (w0b + k < n) acc = acc + static_cast<double>(v[k]);
-            }
+        if (!one_chunk) {
+            __syncthreads();
+            stage(w0, n);
+            __syncthreads();
         }
+        if (owner) each_row(n, [&](double v) { acc = acc + v; });
     }
     const double m = acc / static_cast<double>(a.W);
     double sq = 0.0;
-    const bool one_chunk = a.W <= kWinChunk;
     for (int w0 = 0; w0 < a.W; w0 += kWinChunk) {
         const int n = min(kWinChunk, a.W - w0);
         if (!one_chunk) {
@@ -89,19 +139,11 @@ __global__ void __launch_bounds__(kProxyThreads) build_proxies_kernel(ProxyArgs 
             __syncthreads();
         }
         if (owner) {
-            for (int w0b = 0; w0b < n; w0b += kStatBatch) {
-                float v[kStatBatch];
-#pragma unroll
-                for (int k = 0; k < kStatBatch; ++k) v[k] = w0b + k < n ? win[(w0b + k) * kBlockDims + tid] : 0.f;
-#pragma unroll
-                for (int k = 0; k < kStatBatch; ++k) {
-                    if (w0b + k < n) {
-                        const double diff = static_cast<double>(v[k]) - m;
-                        const double dd = diff * diff;
-                        sq = sq + dd;
-                    }
-                }
-            }
+            each_row(n, [&](double v) {
+                const double diff = v - m;
+                const double dd = diff * diff;
+                sq = sq + dd;
+            });
         }
     }
     if (owner) {
@@ -109,34 +151,16 @@ __global__ void __launch_bounds__(kProxyThreads) build_proxies_kernel(ProxyArgs 
         const double sg = sqrt(sq / static_cast<double>(a.W - a.ddof));
         mu[j] = m;
         gs[j] = a.gamma * sg;
-        if (a.stats != nullptr) {
+        if (a.stats != nullptr && part == 0) {
             double* st = a.stats + (static_cast<int64_t>(b) * a.Hq + h) * 2 * d;
             st[j] = m;
             st[d + j] = sg;
         }
     }
-    // Draws of this thread's first kPreItems items, made before the
-    // statistics are published (they do not depend on them): every wave
-    // draws while the statistics lanes run their serial sums.  The draws are
-    // fp32 values, so keeping them as fp32 and widening later is exact.
-    constexpr int kPreItems = 4;
-    const int n_items = a.P * qpb;
-    float zp[kPreItems][4], zp2[kPreItems][4];
     if (one_chunk) {
 #pragma unroll
-        for (int k = 0; k < kPreItems; ++k) {
-            const int item = tid + k * kProxyThreads;
-            if (item < n_items) {
-                const int i = item / qpb, jq = q0 + item % qpb;
-                double z[4];
-                normal_quad(a.key0, a.key1, b, a.layer, h, i, jq, z);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) zp[k][e] = static_cast<float>(z[e]);
-                if (rope) normal_quad(a.key0, a.key1, b, a.layer, h, i, jq + d / 8, z);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) zp2[k][e] = rope ? static_cast<float>(z[e]) : 0.f;
-            }
-        }
+        for (int k = 0; k < kPreItems; ++k)
+            if (first + k * kProxyThreads < n_items) draw(first + k * kProxyThreads, zp[k], zp2[k]);
     }
     __syncthreads();
 
@@ -156,8 +180,8 @@ __global__ void __launch_bounds__(kProxyThreads) build_proxies_kernel(ProxyArgs 
 #pragma unroll
             for (int e = 0; e < 4; ++e) sx[e] = x[e] * a.scale;
             uint2 pk;
-            pk.x = static_cast<uint32_t>(to_bf16(sx[0])) | (static_cast<uint32_t>(to_bf16(sx[1])) << 16);
-            pk.y = static_cast<uint32_t>(to_bf16(sx[2])) | (static_cast<uint32_t>(to_bf16(sx[3])) << 16);
+            pk.x = pack_bf16(static_cast<float>(sx[0]), static_cast<float>(sx[1]));
+            pk.y = pack_bf16(static_cast<float>(sx[2]), static_cast<float>(sx[3]));
             *reinterpret_cast<uint2*>(row + 4 * jq) = pk;
         } else {
             // partner dims j + d/2 come from quad jq + d/8
@@ -169,7 +193,7 @@ __global__ void __launch_bounds__(kProxyThreads) build_proxies_kernel(ProxyArgs 
                 const double t = gs[j] * z2[e];
                 y[e] = mu[j] + t;
             }
-            uint16_t lo[4], hi[4];
+            float lo[4], hi[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int j = 4 * jq + e;
@@ -177,19 +201,16 @@ __global__ void __launch_bounds__(kProxyThreads) build_proxies_kernel(ProxyArgs 
                 const double a0 = x[e] * c, a1 = y[e] * s;
                 const double b0 = y[e] * c, b1 = x[e] * s;
                 const double rl = a0 - a1, rh = b0 + b1;
-                lo[e] = to_bf16(rl * a.scale);
-                hi[e] = to_bf16(rh * a.scale);
+                lo[e] = static_cast<float>(rl * a.scale);
+                hi[e] = static_cast<float>(rh * a.scale);
             }
-            uint2 pl, ph;
-            pl.x = lo[0] | (static_cast<uint32_t>(lo[1]) << 16);
-            pl.y = lo[2] | (static_cast<uint32_t>(lo[3]) << 16);
-            ph.x = hi[0] | (static_cast<uint32_t>(hi[1]) << 16);
-            ph.y = hi[2] | (static_cast<uint32_t>(hi[3]) << 16);
+            const uint2 pl = make_uint2(pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3]));
+            const uint2 ph = make_uint2(pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3]));
             *reinterpret_cast<uint2*>(row + 4 * jq) = pl;
             *reinterpret_cast<uint2*>(row + half + 4 * jq) = ph;
         }
     };
-    int item = tid;
+    int item = first;
     if (one_chunk) {
 #pragma unroll
         for (int k = 0; k < kPreItems; ++k, item += kProxyThreads) {
@@ -200,16 +221,20 @@ __global__ void __launch_bounds__(kProxyThreads) build_proxies_kernel(ProxyArgs 
                     z[e] = static_cast<double>(zp[k][e]);
                     z2[e] = static_cast<double>(zp2[k][e]);
                 }
-                emit(item / qpb, q0 + item % qpb, z, z2);
+                emit(item >> qsh, q0 + (item & (qpb - 1)), z, z2);
             }
         }
     }
     for (; item < n_items; item += kProxyThreads) {
-        const int i = item / qpb, jq = q0 + item % qpb;
-        double z[4], z2[4] = {0.0, 0.0, 0.0, 0.0};
-        normal_quad(a.key0, a.key1, b, a.layer, h, i, jq, z);
-        if (rope) normal_quad(a.key0, a.key1, b, a.layer, h, i, jq + d / 8, z2);
-        emit(i, jq, z, z2);
+        float z1[4], zr[4];
+        draw(item, z1, zr);
+        double z[4], z2[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            z[e] = static_cast<double>(z1[e]);
+            z2[e] = static_cast<double>(zr[e]);
+        }
+        emit(item >> qsh, q0 + (item & (qpb - 1)), z, z2);
     }
 
     // anchor query: window row W-1, all dims, by workgroup 0
@@ -239,7 +264,19 @@ __global__ void __launch_bounds__(kProxyThreads) build_proxies_kernel(ProxyArgs 
 }  // namespace
 
 hipError_t launch_build_proxies(const ProxyArgs& a, hipStream_t s) {
-    dim3 grid(a.d / kBlockDims, a.Hq, a.B);
+    // Few heads leave CUs without a workgroup (4 heads of 64: 16), and one wave a
+    // SIMD has nothing to hide the window's loads and the serial sums behind:
+    // a head's proxies are then shared by several workgroups, which each form
+    // the statistics anew.  More than two workgroups per CU cost more than they
+    // gain.  Measured (us), window loads one at a time and one part / one round
+    // of loads and one part / the parts chosen here: 4 heads of 64, W = 16 9.4 /
+    // 8.7 / 4.2, 28 heads of 128, W = 32 12.3 / 10.2 / 9.1 (1024 workgroups 10.7,
+    // 2048 15.5); 4 x 28 heads, W = 64 25.3 / 20.8, one part either way.
+    const int blocks = a.d / kBlockDims;
+    const int64_t n = static_cast<int64_t>(blocks) * a.Hq * a.B;
+    int parts = 1;
+    while (n * parts < 2 * kPlanCus && a.P / (2 * parts) >= 32) parts *= 2;
+    dim3 grid(blocks * parts, a.Hq, a.B);
     const size_t lds = 2 * static_cast<size_t>(a.d) * sizeof(double) +
                        static_cast<size_t>(kWinChunk) * kBlockDims * sizeof(float);
     hipLaunchKernelGGL(build_proxies_kernel, grid, dim3(kProxyThreads), lds, s, a);
