@@ -192,8 +192,6 @@ int check_score_outputs(const mmskv_params* p, const float* gm, const float* mas
     return MMSKV_OK;
 }
 
-constexpr int kHiddenChunk = 256;   // tokens per partial sum of the hidden statistics
-
 int check_hshape(const mmskv_hshape* s) {
     if (s == nullptr) return MMSKV_EINVAL;
     if (s->B < 1 || s->B > 65535 || s->T < 1 || s->D < 8 || s->D % 8 != 0) return MMSKV_EINVAL;
@@ -201,7 +199,8 @@ int check_hshape(const mmskv_hshape* s) {
 }
 
 size_t hidden_stats_ws(const mmskv_hshape* s) {
-    const size_t chunks = (static_cast<size_t>(s->T) + kHiddenChunk - 1) / kHiddenChunk;
+    const size_t chunk = static_cast<size_t>(hidden_chunk(s->B, s->T, s->D));
+    const size_t chunks = (static_cast<size_t>(s->T) + chunk - 1) / chunk;
     return align_up(static_cast<size_t>(s->B) * chunks * s->D * sizeof(double2));
 }
 
@@ -696,8 +695,8 @@ int mmshiftkv_hidden_stats(const mmskv_hshape* shape, int32_t std_ddof, const vo
     a.B = shape->B;
     a.T = shape->T;
     a.D = shape->D;
-    a.chunk = kHiddenChunk;
-    a.n_chunks = (shape->T + kHiddenChunk - 1) / kHiddenChunk;
+    a.chunk = hidden_chunk(shape->B, shape->T, shape->D);
+    a.n_chunks = (shape->T + a.chunk - 1) / a.chunk;
     a.ddof = std_ddof;
     a.partial = static_cast<double2*>(workspace);
     a.stats = stats;

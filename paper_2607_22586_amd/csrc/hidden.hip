@@ -5,7 +5,8 @@
 //
 // hidden_stats   per (batch row, feature): S = sum h and SS = sum h^2 over
 //                chunks of tokens (token order inside a chunk, one thread
-//                per 8 features, fp64), then the chunk sums in chunk order;
+//                per 8 features, fp64), then the chunk sums in eight parts of
+//                chunk order;
 //                mean = S/T, std = sqrt((SS - S*mean)/(T - ddof)).
 // hidden_proxies x = mu + (gamma*sigma) z per (batch row, sample, feature),
 //                z from the counter-based generator with the head field set
@@ -63,19 +64,17 @@ __device__ __forceinline__ void unpack_bf16x8(const u32x4& r, double (&v)[kStatV
     }
 }
 
-// 8 consecutive fp32 features of one token as fp64.
-__device__ __forceinline__ void load8_f32(const HiddenArgs& a, int64_t off, double (&v)[kStatVec]) {
-    const float4 x = *reinterpret_cast<const float4*>(static_cast<const float*>(a.hidden) + off);
-    const float4 y = *reinterpret_cast<const float4*>(static_cast<const float*>(a.hidden) + off + 4);
-    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-    v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
+__device__ __forceinline__ void unpack_f32x8(const float4 (&r)[2], double (&v)[kStatVec]) {
+    v[0] = r[0].x; v[1] = r[0].y; v[2] = r[0].z; v[3] = r[0].w;
+    v[4] = r[1].x; v[5] = r[1].y; v[6] = r[1].z; v[7] = r[1].w;
 }
 
 // Chunk sums: grid (n_chunks, ceil(D / (8*64)), B); thread j owns features
 // [8j, 8j+8) of the block and sums them over the chunk's tokens in token
-// order.  bf16 rows: the raw 16-byte loads of the next kStatFlight tokens
-// are issued before the current ones are summed (two register sets used in
-// turn), so up to two groups of loads are in flight per thread.
+// order.  The raw loads of the next group of tokens (kStatFlight of bf16 rows,
+// half as many of fp32 rows) are issued before the current ones are summed
+// (two register sets used in turn), so up to two groups of loads are in flight
+// per thread.
 __global__ void __launch_bounds__(kStatThreads) hidden_stats_partial_kernel(HiddenArgs a) {
     const int c = blockIdx.x, b = blockIdx.z;
     const int j0 = (static_cast<int>(blockIdx.y) * kStatThreads + static_cast<int>(threadIdx.x)) * kStatVec;
@@ -85,65 +84,89 @@ __global__ void __launch_bounds__(kStatThreads) hidden_stats_partial_kernel(Hidd
 #pragma unroll
     for (int e = 0; e < kStatVec; ++e) { s[e] = 0.0; ss[e] = 0.0; }
     const int64_t base = static_cast<int64_t>(b) * a.sb + j0;
-    if (a.dtype == 1) {
-        const uint16_t* h = static_cast<const uint16_t*>(a.hidden) + base;
-        auto fetch = [&](int t, u32x4 (&r)[kStatFlight]) {
+    // tokens [t0, t1) in groups of F, load(t, raw) and unpack(raw, values) per token
+    auto sweep = [&](auto& ra, auto& rb, auto load, auto unpack) {
+        constexpr int F = sizeof(ra) / sizeof(ra[0]);
+        auto fetch = [&](int t, auto& r) {
 #pragma unroll
-            for (int u = 0; u < kStatFlight; ++u)
-                if (t + u < t1) r[u] = *reinterpret_cast<const u32x4*>(h + static_cast<int64_t>(t + u) * a.st);
+            for (int u = 0; u < F; ++u)
+                if (t + u < t1) load(t + u, r[u]);
         };
-        auto sum = [&](int t, const u32x4 (&r)[kStatFlight]) {
+        auto sum = [&](int t, auto& r) {
 #pragma unroll
-            for (int u = 0; u < kStatFlight; ++u) {
+            for (int u = 0; u < F; ++u) {
                 if (t + u < t1) {
                     double v[kStatVec];
-                    unpack_bf16x8(r[u], v);
+                    unpack(r[u], v);
                     accum_token(v, s, ss);
                 }
             }
         };
         // two register sets, A for tokens [t, t+F), B for [t+F, t+2F)
-        u32x4 ra[kStatFlight], rb[kStatFlight];
         fetch(t0, ra);
-        for (int t = t0; t < t1; t += 2 * kStatFlight) {
-            if (t + kStatFlight < t1) fetch(t + kStatFlight, rb);
+        for (int t = t0; t < t1; t += 2 * F) {
+            if (t + F < t1) fetch(t + F, rb);
             sum(t, ra);
-            if (t + 2 * kStatFlight < t1) fetch(t + 2 * kStatFlight, ra);
-            if (t + kStatFlight < t1) sum(t + kStatFlight, rb);
+            if (t + 2 * F < t1) fetch(t + 2 * F, ra);
+            if (t + F < t1) sum(t + F, rb);
         }
+    };
+    if (a.dtype == 1) {
+        const uint16_t* h = static_cast<const uint16_t*>(a.hidden) + base;
+        u32x4 ra[kStatFlight], rb[kStatFlight];
+        sweep(ra, rb, [&](int t, u32x4& r) { r = *reinterpret_cast<const u32x4*>(h + static_cast<int64_t>(t) * a.st); },
+              [](const u32x4& r, double (&v)[kStatVec]) { unpack_bf16x8(r, v); });
     } else {
-        for (int t = t0; t < t1; ++t) {
-            double v[kStatVec];
-            load8_f32(a, base + static_cast<int64_t>(t) * a.st, v);
-            accum_token(v, s, ss);
-        }
+        const float* h = static_cast<const float*>(a.hidden) + base;
+        float4 ra[kStatFlight / 2][2], rb[kStatFlight / 2][2];
+        sweep(ra, rb,
+              [&](int t, float4 (&r)[2]) {
+                  const float4* p = reinterpret_cast<const float4*>(h + static_cast<int64_t>(t) * a.st);
+                  r[0] = p[0];
+                  r[1] = p[1];
+              },
+              [](const float4 (&r)[2], double (&v)[kStatVec]) { unpack_f32x8(r, v); });
     }
     double2* out = a.partial + (static_cast<int64_t>(b) * a.n_chunks + c) * a.D + j0;
 #pragma unroll
     for (int e = 0; e < kStatVec; ++e) out[e] = make_double2(s[e], ss[e]);
 }
 
-// Chunk sums in chunk order -> mean, std: grid (ceil(D/256), B).
-__global__ void __launch_bounds__(256) hidden_stats_final_kernel(HiddenArgs a) {
-    const int j = static_cast<int>(blockIdx.x) * 256 + static_cast<int>(threadIdx.x), b = blockIdx.y;
-    if (j >= a.D) return;
-    const double2* p = a.partial + static_cast<int64_t>(b) * a.n_chunks * a.D + j;
+// Chunk sums -> mean, std: grid (ceil(D/32), B); thread (feature, eighth e of
+// the chunks) adds its chunks in order, kFinalBatch of them fetched at once
+// (their latencies overlap), then one thread per feature the eighths in order.
+constexpr int kFinalFeatures = 32, kFinalParts = 8;
+__global__ void __launch_bounds__(kFinalFeatures * kFinalParts) hidden_stats_final_kernel(HiddenArgs a) {
+    __shared__ double2 part[kFinalParts][kFinalFeatures];
+    const int f = static_cast<int>(threadIdx.x) % kFinalFeatures, e = static_cast<int>(threadIdx.x) / kFinalFeatures;
+    const int j = static_cast<int>(blockIdx.x) * kFinalFeatures + f, b = blockIdx.y;
     double S = 0.0, SS = 0.0;
-    // kFinalBatch chunk partials fetched at once (their latencies overlap),
-    // then added in chunk order
-    constexpr int kFinalBatch = 16;
-    for (int c0 = 0; c0 < a.n_chunks; c0 += kFinalBatch) {
-        double2 v[kFinalBatch];
+    if (j < a.D) {
+        const double2* p = a.partial + static_cast<int64_t>(b) * a.n_chunks * a.D + j;
+        const int c0 = static_cast<int>(static_cast<int64_t>(a.n_chunks) * e / kFinalParts);
+        const int c1 = static_cast<int>(static_cast<int64_t>(a.n_chunks) * (e + 1) / kFinalParts);
+        constexpr int kFinalBatch = 8;
+        for (int c = c0; c < c1; c += kFinalBatch) {
+            double2 v[kFinalBatch];
 #pragma unroll
-        for (int u = 0; u < kFinalBatch; ++u)
-            if (c0 + u < a.n_chunks) v[u] = p[static_cast<int64_t>(c0 + u) * a.D];
+            for (int u = 0; u < kFinalBatch; ++u)
+                if (c + u < c1) v[u] = p[static_cast<int64_t>(c + u) * a.D];
 #pragma unroll
-        for (int u = 0; u < kFinalBatch; ++u) {
-            if (c0 + u < a.n_chunks) {
-                S = S + v[u].x;
-                SS = SS + v[u].y;
+            for (int u = 0; u < kFinalBatch; ++u) {
+                if (c + u < c1) {
+                    S = S + v[u].x;
+                    SS = SS + v[u].y;
+                }
             }
         }
+    }
+    part[e][f] = make_double2(S, SS);
+    __syncthreads();
+    if (e > 0 || j >= a.D) return;
+#pragma unroll
+    for (int q = 1; q < kFinalParts; ++q) {
+        S = S + part[q][f].x;
+        SS = SS + part[q][f].y;
     }
     const double mean = S / static_cast<double>(a.T);
     const double sm = S * mean;
@@ -157,9 +180,12 @@ __global__ void __launch_bounds__(256) hidden_stats_final_kernel(HiddenArgs a) {
 __global__ void __launch_bounds__(256) hidden_proxies_kernel(HiddenArgs a) {
     const int b = blockIdx.y;
     const int quads = a.D / 4;
-    const int64_t item = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (item >= static_cast<int64_t>(a.P) * quads) return;
-    const int i = static_cast<int>(item / quads), jq = static_cast<int>(item % quads);
+    const int64_t item0 = static_cast<int64_t>(blockIdx.x) * 256;
+    if (item0 + threadIdx.x >= static_cast<int64_t>(a.P) * quads) return;
+    // (the 64-bit division once per workgroup, in scalars)
+    const int i0 = static_cast<int>(item0 / quads);
+    const uint32_t r = static_cast<uint32_t>(item0 - static_cast<int64_t>(i0) * quads) + threadIdx.x;
+    const int i = i0 + static_cast<int>(r / static_cast<uint32_t>(quads)), jq = static_cast<int>(r % static_cast<uint32_t>(quads));
     const double* mu = a.stats + (static_cast<int64_t>(b) * 2) * a.D;
     const double* sg = a.stats + (static_cast<int64_t>(b) * 2 + 1) * a.D;
     double z[4];
@@ -609,17 +635,27 @@ hipError_t launch_wide(const ProjectArgs& p, hipStream_t s) {
 struct WideForm {
     int m, n, stages, cost;
 };
-constexpr WideForm kWide[] = {{128, 224, 2, 104}, {128, 128, 3, 68}, {64, 128, 4, 44}, {64, 64, 3, 33}};
+constexpr WideForm kWide[] = {{128, 224, 3, 104}, {128, 128, 3, 68}, {64, 128, 4, 44}, {64, 64, 3, 33}};
 
 }  // namespace
+
+// Tokens per chunk: 256, and fewer (a chunk has its own wave per 512 features)
+// while the chunks leave most CUs without a wave, down to 32, below which the
+// partials cost what the shorter chains gain.
+int hidden_chunk(int B, int T, int D) {
+    const int64_t waves = static_cast<int64_t>(B) * ((D + kStatThreads * kStatVec - 1) / (kStatThreads * kStatVec));
+    int chunk = 256;
+    while (chunk > 32 && waves * ((T + chunk - 1) / chunk) < 4 * kPlanCus) chunk /= 2;
+    return chunk;
+}
 
 hipError_t launch_hidden_stats(const HiddenArgs& a, hipStream_t s) {
     dim3 g1(a.n_chunks, (a.D + kStatThreads * kStatVec - 1) / (kStatThreads * kStatVec), a.B);
     hipLaunchKernelGGL(hidden_stats_partial_kernel, g1, dim3(kStatThreads), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    dim3 g2((a.D + 255) / 256, a.B);
-    hipLaunchKernelGGL(hidden_stats_final_kernel, g2, dim3(256), 0, s, a);
+    dim3 g2((a.D + kFinalFeatures - 1) / kFinalFeatures, a.B);
+    hipLaunchKernelGGL(hidden_stats_final_kernel, g2, dim3(kFinalFeatures * kFinalParts), 0, s, a);
     return hipGetLastError();
 }
 
@@ -633,10 +669,12 @@ hipError_t launch_hidden_proxies(const HiddenArgs& a, hipStream_t s) {
 hipError_t launch_project(const ProjectArgs& p, hipStream_t s) {
     // the tile size with the smallest modelled time, among those that divide
     // the matrix and whose stages a reduction of K fills.  Measured (us), the
-    // 128 x 128 tiles in two stages that all but the 128 x 224 ones replace
-    // against the choice made here, M x N = K: 512 x 3584 47 -> 25, 1024 x
-    // 3584 49 -> 38, 2048 x 3584 with rotary tables 68 -> 57, 512 x 2048 24 ->
-    // 10.7, 1024 x 2048 25.6 -> 14.5, 2048 x 2048 27.5 -> 22.6.
+    // 128 x 128 and (2048 x 3584) 128 x 224 tiles in two stages that these
+    // replace against the choice made here, M x N with K = N: 512 x 3584 47 ->
+    // 25, 1024 x 3584 49 -> 37, 512 x 2048 24 -> 10.6, 1024 x 2048 25.6 -> 14.9,
+    // 2048 x 2048 27.5 -> 22.5; 2048 x 3584 with rotary tables 68 -> 56, and
+    // within a layer, its weights coming from memory, 77 -> 59 (71 with two
+    // stages).
     int best = -1;
     int64_t best_cost = 0;
     if (p.K % kWK == 0 && p.K <= (1 << 20)) {          // (lane offsets within 32 bits)
@@ -652,7 +690,7 @@ hipError_t launch_project(const ProjectArgs& p, hipStream_t s) {
         }
     }
     switch (best) {
-        case 0: return launch_wide<4, 7, 2>(p, s);
+        case 0: return launch_wide<4, 7, 3>(p, s);
         case 1: return launch_wide<4, 4, 3>(p, s);
         case 2: return launch_wide<2, 4, 4>(p, s);
         case 3: return launch_wide<2, 2, 3>(p, s);

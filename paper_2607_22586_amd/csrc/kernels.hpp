@@ -176,6 +176,7 @@ hipError_t launch_select(const SelectArgs& a, int stages, hipStream_t s);
 int select_kpt(int T);
 inline int64_t select_digit_stride(int T) { return static_cast<int64_t>(select_kpt(T)) * 1024; }
 hipError_t launch_gather(const GatherArgs& a, hipStream_t s);
+int hidden_chunk(int B, int T, int D);       // tokens per partial sum of the hidden statistics
 hipError_t launch_hidden_stats(const HiddenArgs& a, hipStream_t s);
 hipError_t launch_hidden_proxies(const HiddenArgs& a, hipStream_t s);
 hipError_t launch_project(const ProjectArgs& p, hipStream_t s);

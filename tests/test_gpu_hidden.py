@@ -87,7 +87,10 @@ def check_projection(gpu_bits, hp_bits, wq_bits, Hq, rope=None, min_exact=0.99):
 # ---------------------------------------------------------------- Eq. 4
 @pytest.mark.parametrize("B,T,D,dtype,ddof,pad", [
     (1, 1, 64, "bf16", 0, 0), (2, 300, 200, "f32", 1, 0), (1, 777, 3584, "bf16", 0, 0),
-    (3, 513, 136, "bf16", 1, 16), (2, 256, 8, "f32", 0, 4)])
+    (3, 513, 136, "bf16", 1, 16), (2, 256, 8, "f32", 0, 4),
+    # chunks of 32, 64, 128 and 256 tokens, ragged last chunks and groups of loads, idle parts of the merge
+    (1, 33, 72, "f32", 0, 0), (1, 4100, 3584, "f32", 0, 0), (2, 9001, 1032, "bf16", 0, 8), (4, 5003, 3584, "f32", 1, 0),
+    (4, 9999, 3584, "bf16", 0, 0), (1, 16384, 520, "bf16", 0, 0)])
 def test_hidden_stats_within_fp64_bound(B, T, D, dtype, ddof, pad):
     x = wl.custom_hidden(B, T, D + pad, 1, 8, dtype=dtype, seed=T + D)["hidden"]
     h = x.to(DEV)[:, :, :D]                       # strided view when pad > 0
@@ -123,12 +126,13 @@ def test_hidden_proxies_bit_exact(B, P, D, gamma, layer):
 @pytest.mark.parametrize("B,P,D,Hq,d,rope", [
     (2, 64, 3584, 28, 128, False), (3, 40, 200, 3, 64, False), (1, 50, 136, 2, 128, True),
     (2, 33, 3584, 4, 64, True), (1, 1, 8, 1, 64, False),
-    # full 128 x 224 tiles without rotation, 2, 3 and 5 k steps of 64
+    # too few k steps of 64 for any full tile (2), and 3 and 5
     (2, 128, 128, 7, 64, False), (1, 128, 192, 14, 64, False), (1, 256, 320, 7, 64, False),
-    # the same with rotation: the pairs of a tile are not whole heads
+    # the same with rotation
     (2, 128, 128, 7, 64, True), (1, 128, 192, 14, 64, True), (1, 256, 128, 7, 128, True),
-    # and at 3 and 5 k steps, 4 rounds of the smallest tiles
-    (7, 1024, 192, 7, 64, False), (7, 1024, 320, 7, 64, True),
+    # 128 x 224 tiles (3 stages), 4 rounds of the smallest tiles: their least
+    # reduction, one and two steps more; the pairs of a tile are not whole heads
+    (7, 1024, 192, 7, 64, False), (7, 1024, 256, 7, 64, True), (7, 1024, 320, 7, 64, True),
     # 64 x 64 tiles (3 stages): their least reduction, one step more, one batch row of 512
     (1, 64, 192, 1, 64, False), (2, 64, 256, 3, 64, True), (1, 512, 192, 1, 128, True), (1, 512, 448, 4, 128, False),
     # 64 x 128 tiles (4 stages): 3 x 88 = 264 tiles of 64 x 64, at 4, 5 and 6 steps
