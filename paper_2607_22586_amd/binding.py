@@ -165,12 +165,35 @@ def _strides4(t: torch.Tensor) -> Strides:
     return Strides(t.stride(0), t.stride(1), t.stride(2))
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    # the raw handle, without a Stream object around it
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # (the argument types of the library's functions make a pointer of it)
+    return None if t is None else t.data_ptr()
+
+
+class _on:
+    """The device of a tensor made current around a call, and put back."""
+    __slots__ = ("index", "before")
+
+    def __init__(self, device):
+        self.index = device.index
+
+    def __enter__(self):
+        self.before = torch.cuda._exchange_device(self.index)
+
+    def __exit__(self, *exc):
+        torch.cuda._maybe_exchange_device(self.before)
+        return False
+
+
+def _tables(rope, dev):
+    """(cos, sin) as contiguous fp32 tensors on dev."""
+    return [t if t.dtype == torch.float32 and t.device == dev and t.is_contiguous()
+            else t.to(device=dev, dtype=torch.float32).contiguous() for t in (rope[0], rope[1])]
 
 
 def _shape(B, Hq, Hkv, T, W, d) -> Shape:
@@ -203,9 +226,8 @@ def build_proxies(q_win: torch.Tensor, cfg: SelectionConfig, T: int, Hkv: int, r
         if rp is None:
             tabs += [None, None]
         else:
-            tabs += [rp[0].to(device=dev, dtype=torch.float32).contiguous(),
-                     rp[1].to(device=dev, dtype=torch.float32).contiguous()]
-    with torch.cuda.device(dev):
+            tabs += _tables(rp, dev)
+    with _on(dev):
         rc = load_library().mmshiftkv_build_proxies(
             ctypes.byref(shape), ctypes.byref(prm), _p(q_win), _dtype_code(q_win),
             ctypes.byref(_strides4(q_win)), *[_p(t) for t in tabs], _p(proxies), _p(q_last),
@@ -231,7 +253,7 @@ def hidden_stats(hidden: torch.Tensor, std_ddof: int = 0, out=None, workspace=No
     if st.dtype != torch.float64 or not st.is_contiguous() or tuple(st.shape) != (B, 2, D):
         raise ValueError("preallocated stats do not match")
     ws = workspace if workspace is not None else _ws(hidden_stats_workspace(B, T, D), dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         rc = load_library().mmshiftkv_hidden_stats(
             ctypes.byref(hs), int(std_ddof), _p(hidden), _dtype_code(hidden), hidden.stride(0),
             hidden.stride(1), _p(st), _p(ws), ws.numel() * ws.element_size(), _stream(dev))
@@ -248,7 +270,7 @@ def hidden_proxies(stats: torch.Tensor, cfg: SelectionConfig, T: int = 1, out=No
     hp = out if out is not None else torch.empty((B, cfg.P, D), dtype=torch.bfloat16, device=dev)
     if hp.dtype != torch.bfloat16 or not hp.is_contiguous() or tuple(hp.shape) != (B, cfg.P, D):
         raise ValueError("preallocated samples do not match")
-    with torch.cuda.device(dev):
+    with _on(dev):
         rc = load_library().mmshiftkv_hidden_proxies(ctypes.byref(HShape(B, int(T), D)),
                                                      ctypes.byref(cfg.c_params()), _p(stats), _p(hp),
                                                      _stream(dev))
@@ -273,9 +295,8 @@ def project_proxies(hp: torch.Tensor, wq: torch.Tensor, Hq: int, rope=None, out=
         raise ValueError("preallocated proxies do not match")
     tabs = [None, None]
     if rope is not None:
-        tabs = [rope[0].to(device=dev, dtype=torch.float32).contiguous(),
-                rope[1].to(device=dev, dtype=torch.float32).contiguous()]
-    with torch.cuda.device(dev):
+        tabs = _tables(rope, dev)
+    with _on(dev):
         rc = load_library().mmshiftkv_project_proxies(ctypes.byref(HShape(B, 1, D)), P, int(Hq), d, _p(hp),
                                                       _p(wq), _p(tabs[0]), _p(tabs[1]), _p(pr), _stream(dev))
     _check("mmshiftkv_project_proxies", rc)
@@ -316,10 +337,11 @@ def _score_call(which: str, proxies, q_last, k, cfg, W, out: ScoreOut | None, wo
     shape = _shape(B, Hq, Hkv, T, W, d)
     prm = cfg.c_params()
     lib = load_library()
-    need = int(lib.mmshiftkv_score_workspace(ctypes.byref(shape), ctypes.byref(prm)))
-    ws = workspace if workspace is not None else _ws(need, dev)
+    ws = workspace
+    if ws is None:
+        ws = _ws(lib.mmshiftkv_score_workspace(ctypes.byref(shape), ctypes.byref(prm)), dev)
     strides = _strides4(k)
-    with torch.cuda.device(dev):
+    with _on(dev):
         if which in ("lse", "lse_blocks", "lse_merge"):
             name = "mmshiftkv_score_" + which
             rc = getattr(lib, name)(ctypes.byref(shape), ctypes.byref(prm), _p(proxies), _p(q_last),
@@ -358,7 +380,7 @@ def score_noalloc(proxies, q_last, k, cfg: SelectionConfig, out: ScoreOut, W: in
         raise ValueError("proxies and q_last must be contiguous")
     shape = _shape(B, Hq, Hkv, T, W, d)
     prm = cfg.c_params()
-    with torch.cuda.device(dev):
+    with _on(dev):
         rc = load_library().mmshiftkv_score_noalloc(
             ctypes.byref(shape), ctypes.byref(prm), _p(proxies), _p(q_last), _p(k), _dtype_code(k),
             ctypes.byref(_strides4(k)), _p(out.group_mass), _p(out.mass), _p(out.anchor), _stream(dev))
@@ -403,8 +425,9 @@ def select_topk(s: ScoreOut, cfg: SelectionConfig, budget: int, c_max: int | Non
     shape = _shape(B, Hq, Hkv, T, 0, 0)           # W and d are not read by the selection
     prm = cfg.c_params()
     lib = load_library()
-    need = int(lib.mmshiftkv_select_workspace(ctypes.byref(shape), ctypes.byref(prm)))
-    ws = workspace if workspace is not None else _ws(need, dev)
+    ws = workspace
+    if ws is None:
+        ws = _ws(lib.mmshiftkv_select_workspace(ctypes.byref(shape), ctypes.byref(prm)), dev)
     if out is None:
         out = Selected(torch.empty((B, Hkv, c_max), dtype=torch.int32, device=dev),
                        torch.empty((B, Hkv), dtype=torch.int32, device=dev),
@@ -413,7 +436,7 @@ def select_topk(s: ScoreOut, cfg: SelectionConfig, budget: int, c_max: int | Non
         budgets = budgets.to(device=dev, dtype=torch.int32).contiguous()
     nbytes = ws.numel() * ws.element_size()
     S, Pm = ctypes.byref(shape), ctypes.byref(prm)
-    with torch.cuda.device(dev):
+    with _on(dev):
         if stage is None:
             name = "mmshiftkv_select_topk"
             rc = lib.mmshiftkv_select_topk(S, Pm, _p(s.group_mass), _p(s.mass), _p(s.anchor), _p(budgets),
@@ -455,12 +478,13 @@ def decode_check(q_dec: torch.Tensor, k: torch.Tensor, sel: Selected, k_out: tor
     c_max = sel.idx.shape[2]
     shape = _shape(B, Hq, Hkv, T, 1, d)
     lib = load_library()
-    need = int(lib.mmshiftkv_decode_workspace(ctypes.byref(shape), int(n_dec)))
-    ws = workspace if workspace is not None else _ws(need, dev)
+    ws = workspace
+    if ws is None:
+        ws = _ws(lib.mmshiftkv_decode_workspace(ctypes.byref(shape), int(n_dec)), dev)
     if out is None:
         out = (torch.empty((B, Hq, n_dec), dtype=torch.float32, device=dev),
                torch.empty((B, Hq, n_dec, d), dtype=torch.float32, device=dev))
-    with torch.cuda.device(dev):
+    with _on(dev):
         rc = lib.mmshiftkv_decode_check(ctypes.byref(shape), int(n_dec), _p(q_dec), _p(k), _dtype_code(k),
                                         ctypes.byref(_strides4(k)), _p(sel.idx), _p(sel.counts), c_max,
                                         _p(k_out), _p(v_out), _p(out[0]), _p(out[1]), _p(ws),
@@ -479,7 +503,7 @@ def window_rows(q_win: torch.Tensor, n: int, T: int, Hkv: int):
     rows = torch.empty((B, Hq, n, d), dtype=torch.bfloat16, device=dev)
     ql = torch.empty((B, Hq, d), dtype=torch.bfloat16, device=dev)
     shape = _shape(B, Hq, Hkv, T, W, d)
-    with torch.cuda.device(dev):
+    with _on(dev):
         rc = load_library().mmshiftkv_window_rows(ctypes.byref(shape), int(n), _p(q_win), _dtype_code(q_win),
                                                   ctypes.byref(_strides4(q_win)), _p(rows), _p(ql), _stream(dev))
     _check("mmshiftkv_window_rows", rc)
@@ -490,9 +514,11 @@ def shape_scores(mass: torch.Tensor | None, kind: int, B: int, Hkv: int, T: int,
                  sinks: int = 0, out: torch.Tensor | None = None, device=None) -> torch.Tensor:
     """mmshiftkv_shape_scores: per-key baseline scores [B, Hkv, T] fp32."""
     dev = _dev(mass) if mass is not None else torch.device(device if device is not None else "cuda:0")
+    if dev.index is None:
+        dev = torch.device("cuda", torch.cuda.current_device())
     score = out if out is not None else torch.empty((B, Hkv, T), dtype=torch.float32, device=dev)
     shape = _shape(B, 0, Hkv, T, 0, 0)            # only B, Hkv and T are read
-    with torch.cuda.device(dev):
+    with _on(dev):
         rc = load_library().mmshiftkv_shape_scores(ctypes.byref(shape), int(kind), int(window), int(pool), int(sinks),
                                                    _p(mass), _p(score), _stream(dev))
     _check("mmshiftkv_shape_scores", rc)
@@ -545,7 +571,7 @@ def gather_kv(k: torch.Tensor, v: torch.Tensor, sel: Selected, out=None):
     if out is None:
         out = (torch.empty((B, Hkv, c_max, d), dtype=k.dtype, device=dev),
                torch.empty((B, Hkv, c_max, d), dtype=k.dtype, device=dev))
-    with torch.cuda.device(dev):
+    with _on(dev):
         rc = load_library().mmshiftkv_gather_kv(
             ctypes.byref(shape), _p(k), _p(v), _dtype_code(k), ctypes.byref(_strides4(k)),
             ctypes.byref(_strides4(v)), _p(sel.idx), _p(sel.counts), c_max, _p(out[0]), _p(out[1]),
