@@ -537,8 +537,7 @@ def baseline_select(name: str, q_win, k, v, budget: int, seed: int = 0, layer: i
     Hq, W = q_win.shape[1], q_win.shape[2]
     dev = _dev(k)
     sel_cfg = SelectionConfig(mode=MMSKV_MASS, keep_last=False, seed=seed, layer=layer)
-    mass = None
-    anchor = torch.zeros((B, Hkv, T), dtype=torch.float32, device=dev)
+    mass = anchor = None                         # (the anchor is not read in MASS mode)
     if name == "snapkv":
         rows, ql = window_rows(q_win, window, T, Hkv)
         cfg = SelectionConfig(P=window, G=1, mode=MMSKV_MASS, seed=seed, layer=layer)

@@ -37,10 +37,10 @@ __device__ __forceinline__ bf16x8 load_f32_as_bf16x8(const float* p) {
     float4 a = *reinterpret_cast<const float4*>(p);
     float4 b = *reinterpret_cast<const float4*>(p + 4);
     u32x4 v;
-    v[0] = f32_to_bf16_bits(a.x) | (f32_to_bf16_bits(a.y) << 16);
-    v[1] = f32_to_bf16_bits(a.z) | (f32_to_bf16_bits(a.w) << 16);
-    v[2] = f32_to_bf16_bits(b.x) | (f32_to_bf16_bits(b.y) << 16);
-    v[3] = f32_to_bf16_bits(b.z) | (f32_to_bf16_bits(b.w) << 16);
+    v[0] = pack_bf16(a.x, a.y);
+    v[1] = pack_bf16(a.z, a.w);
+    v[2] = pack_bf16(b.x, b.y);
+    v[3] = pack_bf16(b.z, b.w);
     return __builtin_bit_cast(bf16x8, v);
 }
 

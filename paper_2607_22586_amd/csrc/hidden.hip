@@ -190,18 +190,16 @@ __global__ void __launch_bounds__(256) hidden_proxies_kernel(HiddenArgs a) {
     const double* sg = a.stats + (static_cast<int64_t>(b) * 2 + 1) * a.D;
     double z[4];
     normal_quad(a.key0, a.key1, b, a.layer, -1, i, jq, z);
-    uint16_t o[4];
+    float o[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int j = 4 * jq + e;
         const double gs = a.gamma * sg[j];
         const double t = gs * z[e];
         const double x = mu[j] + t;
-        o[e] = static_cast<uint16_t>(f32_to_bf16_bits(static_cast<float>(x)));
+        o[e] = static_cast<float>(x);
     }
-    uint2 pk;
-    pk.x = o[0] | (static_cast<uint32_t>(o[1]) << 16);
-    pk.y = o[2] | (static_cast<uint32_t>(o[3]) << 16);
+    const uint2 pk = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
     *reinterpret_cast<uint2*>(a.hp + (static_cast<int64_t>(b) * a.P + i) * a.D + 4 * jq) = pk;
 }
 
@@ -249,12 +247,11 @@ __device__ __forceinline__ void gemm_store(const GemmStage& st, u32x4* la, u32x4
     }
 }
 
-// Rotary pair (x0, x1), scaled, as bf16 bits.
-__device__ __forceinline__ void rotate_pair(float x0, float x1, float c, float s, double scale, uint32_t& lo,
-                                            uint32_t& hi) {
+// Rotary pair (x0, x1), scaled.
+__device__ __forceinline__ void rotate_pair(float x0, float x1, float c, float s, double scale, float& lo, float& hi) {
     const float a0 = x0 * c, a1 = x1 * s, b0 = x1 * c, b1 = x0 * s;
-    lo = f32_to_bf16_bits(scaled(a0 - a1, scale));
-    hi = f32_to_bf16_bits(scaled(b0 + b1, scale));
+    lo = scaled(a0 - a1, scale);
+    hi = scaled(b0 + b1, scale);
 }
 
 // Epilogue of a 128 x 128 output tile: the fp32 accumulators (wave (wm, wn)
@@ -300,19 +297,18 @@ __device__ __forceinline__ void project_epilogue(const ProjectArgs& p, const flo
         if (!rope) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                lo[q] = f32_to_bf16_bits(scaled(tile[r * kLd + col + 2 * q], p.scale)) |
-                        (f32_to_bf16_bits(scaled(tile[r * kLd + col + 2 * q + 1], p.scale)) << 16);
+                lo[q] = pack_bf16(scaled(tile[r * kLd + col + 2 * q], p.scale), scaled(tile[r * kLd + col + 2 * q + 1], p.scale));
             *reinterpret_cast<u32x4*>(out + e) = lo;
         } else {
-            uint32_t l16[8], h16[8];
+            float lx[8], hx[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q)
                 rotate_pair(tile[r * kLd + col + q], tile[r * kLd + col + half + q], p.cos[e + q], p.sin[e + q], p.scale,
-                            l16[q], h16[q]);
+                            lx[q], hx[q]);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                lo[q] = l16[2 * q] | (l16[2 * q + 1] << 16);
-                hi[q] = h16[2 * q] | (h16[2 * q + 1] << 16);
+                lo[q] = pack_bf16(lx[2 * q], lx[2 * q + 1]);
+                hi[q] = pack_bf16(hx[2 * q], hx[2 * q + 1]);
             }
             *reinterpret_cast<u32x4*>(out + e) = lo;
             *reinterpret_cast<u32x4*>(out + e + half) = hi;
@@ -589,15 +585,15 @@ __global__ void __launch_bounds__(kGemmThreads) project_wide_kernel(ProjectArgs 
             const int m = m0 + r, pr = n0 / 2 + c;
             const int bb = m / p.P, i = m % p.P, h = pr / half, e = pr % half;
             const float* src = tile + r * T::kLd + c;
-            uint32_t l16[8], h16[8];
+            float lx[8], hx[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q)
-                rotate_pair(src[q], src[T::kN / 2 + q], p.cos[e + q], p.sin[e + q], p.scale, l16[q], h16[q]);
+                rotate_pair(src[q], src[T::kN / 2 + q], p.cos[e + q], p.sin[e + q], p.scale, lx[q], hx[q]);
             u32x4 lo, hi;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                lo[q] = l16[2 * q] | (l16[2 * q + 1] << 16);
-                hi[q] = h16[2 * q] | (h16[2 * q + 1] << 16);
+                lo[q] = pack_bf16(lx[2 * q], lx[2 * q + 1]);
+                hi[q] = pack_bf16(hx[2 * q], hx[2 * q + 1]);
             }
             uint16_t* out = p.out + ((static_cast<int64_t>(bb) * p.Hq + h) * p.P + i) * p.d + e;
             *reinterpret_cast<u32x4*>(out) = lo;
@@ -614,7 +610,7 @@ __global__ void __launch_bounds__(kGemmThreads) project_wide_kernel(ProjectArgs 
         u32x4 v;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            v[q] = f32_to_bf16_bits(scaled(src[2 * q], p.scale)) | (f32_to_bf16_bits(scaled(src[2 * q + 1], p.scale)) << 16);
+            v[q] = pack_bf16(scaled(src[2 * q], p.scale), scaled(src[2 * q + 1], p.scale));
         *reinterpret_cast<u32x4*>(p.out + ((static_cast<int64_t>(bb) * p.Hq + h) * p.P + i) * p.d + e) = v;
     }
 }
