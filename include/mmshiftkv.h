@@ -273,8 +273,9 @@ typedef struct {
 /* Eq. 4 over hidden [B, T, D] (dtype, element strides sb / st; features
  * contiguous, rows on 16-byte boundaries): per (b, feature) fp64 mean and
  * std with divisor T - std_ddof (std_ddof 0 or 1, T - std_ddof >= 1).  Sums
- * of values and of squares are taken per chunk of 256 tokens in token order,
- * then added in chunk order; var = (SS - S*mean) / (T - std_ddof), negative
+ * of values and of squares are taken per chunk of 32 to 256 tokens (by the
+ * shape) in token order, added in chunk order within eighths of the chunks,
+ * then the eighths in order; var = (SS - S*mean) / (T - std_ddof), negative
  * values clamped to 0.
  *   stats [B, 2, D] fp64 out (mean row, then std row), contiguous
  * Workspace: mmshiftkv_hidden_stats_workspace bytes (256-byte aligned). */
