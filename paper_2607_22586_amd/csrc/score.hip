@@ -725,20 +725,27 @@ __global__ void __launch_bounds__(64 * WAVES) score_lse_kernel(ScoreArgs a) {
     }
 }
 
-// L_row = M + log2(sum_kb S_kb * 2^(M_kb - M)), one thread per row; the
-// partials are fetched kCombineBatch at a time so their latencies overlap.
-constexpr int kCombineBatch = 16;
-__global__ void __launch_bounds__(256) lse_combine_kernel(ScoreArgs a) {
-    const int r = static_cast<int>(blockIdx.x) * 256 + static_cast<int>(threadIdx.x);
+// L_row = M + log2(sum_kb S_kb * 2^(M_kb - M)): four threads per row, each
+// with every fourth key block's partial, kCombineBatch of them fetched at once
+// so that their latencies overlap, then merged through LDS.  Bound by latency
+// and by how few workgroups there are (one thread per row: 60 at 28 query and 4
+// KV heads, so its tail was the next pass's wait): layers of 4096 / 8191 such
+// keys 81.5 -> 77.7 and 112 -> 106.6 us with four.
+constexpr int kCombineBatch = 8, kCombineRows = 64, kCombineParts = 4;
+__global__ void __launch_bounds__(kCombineRows * kCombineParts) lse_combine_kernel(ScoreArgs a) {
+    __shared__ float2 part[kCombineParts][kCombineRows];
+    const int e = static_cast<int>(threadIdx.x) / kCombineRows, x = static_cast<int>(threadIdx.x) % kCombineRows;
+    const int r = static_cast<int>(blockIdx.x) * kCombineRows + x;
     const int head = static_cast<int>(blockIdx.y);
-    if (r >= a.rows_pad) return;
-    const float2* p = a.part + static_cast<int64_t>(head) * a.n_kb * a.rows_pad + r;
+    const float2* p = a.part + static_cast<int64_t>(head) * a.n_kb * a.rows_pad + min(r, a.rows_pad - 1);
     float M = -INFINITY, S = 0.f;
-    for (int kb0 = 0; kb0 < a.n_kb; kb0 += kCombineBatch) {
+    for (int kb0 = e; kb0 < a.n_kb; kb0 += kCombineBatch * kCombineParts) {
         float2 v[kCombineBatch];
 #pragma unroll
-        for (int j = 0; j < kCombineBatch; ++j)
-            v[j] = kb0 + j < a.n_kb ? p[static_cast<int64_t>(kb0 + j) * a.rows_pad] : make_float2(-INFINITY, 0.f);
+        for (int j = 0; j < kCombineBatch; ++j) {
+            const int kb = kb0 + j * kCombineParts;
+            v[j] = kb < a.n_kb ? p[static_cast<int64_t>(kb) * a.rows_pad] : make_float2(-INFINITY, 0.f);
+        }
         float bm = -INFINITY;
 #pragma unroll
         for (int j = 0; j < kCombineBatch; ++j) bm = fmaxf(bm, v[j].x);
@@ -752,7 +759,19 @@ __global__ void __launch_bounds__(256) lse_combine_kernel(ScoreArgs a) {
                 if (v[j].x != -INFINITY) S += v[j].y * exp2f(v[j].x - M);
         }
     }
-    a.lse[static_cast<int64_t>(head) * a.rows_pad + r] = M + log2f(S);
+    part[e][x] = make_float2(M, S);
+    __syncthreads();
+    if (e > 0 || r >= a.rows_pad) return;
+    float Mt = M;
+#pragma unroll
+    for (int q = 1; q < kCombineParts; ++q) Mt = fmaxf(Mt, part[q][x].x);
+    float St = 0.f;
+    if (Mt != -INFINITY) {
+#pragma unroll
+        for (int q = 0; q < kCombineParts; ++q)
+            if (part[q][x].x != -INFINITY) St += part[q][x].y * exp2f(part[q][x].x - Mt);
+    }
+    a.lse[static_cast<int64_t>(head) * a.rows_pad + r] = Mt + log2f(St);
 }
 
 // ---------------------------------------------------------------- pass 2
@@ -1208,8 +1227,8 @@ hipError_t lse_impl(const ScoreArgs& a, int stages, hipStream_t s) {
         if (e != hipSuccess) return e;
     }
     if (stages & kLseMerge) {
-        dim3 g2((a.rows_pad + 255) / 256, a.B * a.Hkv);
-        hipLaunchKernelGGL(lse_combine_kernel, g2, dim3(256), 0, s, a);
+        dim3 g2((a.rows_pad + kCombineRows - 1) / kCombineRows, a.B * a.Hkv);
+        hipLaunchKernelGGL(lse_combine_kernel, g2, dim3(kCombineRows * kCombineParts), 0, s, a);
         return hipGetLastError();
     }
     return hipSuccess;
