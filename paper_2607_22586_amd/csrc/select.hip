@@ -178,10 +178,13 @@ __device__ __forceinline__ bool in_tau_set(uint32_t bits, int t, uint32_t theta,
 // steps, the fraction (lambda * anchor, mostly far below 1) by its octave and
 // 2^digit_q steps an octave; scores of G + 1 or more (lambda * anchor above
 // 1) take the last digit.  MASS mode: 32 steps an octave from 2^-39 to 2^25.
+// A key with the top bit set (a score of -0 or below) is above all others as a
+// number and takes the last digit.
 // (The top bits of the fp64 score would put all votes from 8 to 31, equal
 // steps of the score all keys of one vote, into one bucket.)
 __device__ __forceinline__ uint32_t key_digit(const SelectArgs& a, uint64_t key) {
     const double score = __longlong_as_double(static_cast<long long>(key));
+    if (key >> 63) return 2047u;
     if (a.mode == 0) {
         const double whole = floor(score);
         if (!(whole <= static_cast<double>(a.G))) return 2047u;
@@ -572,18 +575,18 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
     if (listed && n_in <= kTopkRank) {
         // a small bucket: each key's rank (score desc, index asc) among the
         // others by comparison, 8 threads a key, without radix passes
-        int64_t* lk = reinterpret_cast<int64_t*>(cnt[1]);            // [kTopkRank]; not counted into yet
+        uint64_t* lk = reinterpret_cast<uint64_t*>(cnt[1]);          // [kTopkRank]; not counted into yet
         const int n = static_cast<int>(min(n_in, n_list));
-        if (tid < n) lk[tid] = static_cast<int64_t>(key[list[tid]]);
+        if (tid < n) lk[tid] = key[list[tid]];
         __syncthreads();
         const int me = tid >> 3;
         if (me < n) {
-            const int64_t mk = lk[me];
+            const uint64_t mk = lk[me];
             const int32_t mt = list[me];
             uint32_t rank = 0;
 #pragma unroll 4
             for (int i = tid & 7; i < n; i += 8) {
-                const int64_t k = lk[i];
+                const uint64_t k = lk[i];
                 rank += (k > mk || (k == mk && list[i] < mt)) ? 1u : 0u;
             }
 #pragma unroll
@@ -593,31 +596,34 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
         n_in = need = 0;                                 // nothing left to search
     }
     // the bucket's keys of this thread's share of the list
-    int64_t ck[kTopkOwn];
+    uint64_t ck[kTopkOwn];
     int32_t ct[kTopkOwn];
 #pragma unroll
     for (int i = 0; i < kTopkOwn; ++i) {
         const uint32_t at = static_cast<uint32_t>(tid + i * kSelThreads);
         const bool in = listed && at < min(n_in, n_list);
         ct[i] = in ? list[at] : -1;
-        ck[i] = in ? static_cast<int64_t>(key[ct[i]]) : -1;
+        ck[i] = in ? key[ct[i]] : 0ull;
     }
     // f(key) for the bucket's keys: this thread's share of the list, or its own
     auto in_bucket = [&](auto&& f) {
         if (listed) {
 #pragma unroll
             for (int i = 0; i < kTopkOwn; ++i)
-                if (ct[i] >= 0) f(static_cast<uint64_t>(ck[i]));
+                if (ct[i] >= 0) f(ck[i]);
         } else {
             each_mem([&](int j, uint32_t d) {
                 if (d == dg) f(key[t0 + j]);
             });
         }
     };
-    // threshold: {key > theta} plus the first k_eq keys (by index) equal to it
-    int64_t theta = -1;
+    // threshold: {key > theta} plus the first k_eq keys (by index) equal to
+    // it, or the whole bucket.  Keys compare as unsigned numbers, which gives
+    // every bit pattern a place (a score of -0 or below has the top bit set)
+    const bool whole = need >= n_in;
+    uint64_t theta = 0;
     uint32_t k_eq = 0;
-    if (need < n_in) {
+    if (!whole) {
         in_bucket([&](uint64_t kv) { s_first = kv; });   // any one of them
         __syncthreads();
         const uint64_t first = s_first;
@@ -630,7 +636,7 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
         __syncthreads();
         diff = s_diff;
         if (diff == 0) {                                 // all equal: the first `need` by index
-            theta = static_cast<int64_t>(first);
+            theta = first;
             k_eq = need;
         } else {
             const int top = 63 - __clzll(static_cast<long long>(diff));
@@ -651,11 +657,12 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
                 need = s_rem;
                 if (s_cnt == need) {
                     // the rest is taken whole: every key >= its lower bound
-                    theta = static_cast<int64_t>(prefix) - 1;
+                    // (> 0: the bucket is not taken whole)
+                    theta = prefix - 1;
                     break;
                 }
                 if (shift == 0) {
-                    theta = static_cast<int64_t>(prefix);
+                    theta = prefix;
                     k_eq = need;
                     break;
                 }
@@ -669,7 +676,7 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
         // the selected ones of the list, as bits of their owners
         bool take[kTopkOwn];
 #pragma unroll
-        for (int i = 0; i < kTopkOwn; ++i) take[i] = ct[i] >= 0 && ck[i] > theta;
+        for (int i = 0; i < kTopkOwn; ++i) take[i] = ct[i] >= 0 && (whole || ck[i] > theta);
         if (k_eq > 0) {
             // equal keys by index: each counts the equal ones before it
             __syncthreads();                             // every read of the list is done
@@ -703,8 +710,8 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
         uint32_t n_eq = 0;
         each_mem([&](int j, uint32_t d) {
             if (d != dg) return;
-            const int64_t kv = static_cast<int64_t>(key[t0 + j]);
-            n_sel += kv > theta ? 1u : 0u;
+            const uint64_t kv = key[t0 + j];
+            n_sel += whole || kv > theta ? 1u : 0u;
             n_eq += kv == theta ? 1u : 0u;
         });
         if (k_eq > 0) {
@@ -719,8 +726,8 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
             each_mem([&](int j, uint32_t d) {
                 bool take = d > dg;
                 if (d == dg) {
-                    const int64_t kv = static_cast<int64_t>(key[t0 + j]);
-                    take = kv > theta;
+                    const uint64_t kv = key[t0 + j];
+                    take = whole || kv > theta;
                     if (kv == theta && k_eq > 0) {
                         take = true;
                         --k_eq;
