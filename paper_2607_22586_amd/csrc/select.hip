@@ -436,29 +436,43 @@ __global__ void __launch_bounds__(256) clear_hist0_kernel(SelectArgs a) {
 // kernel's counts name the digit bucket that holds the threshold; keys in
 // higher buckets are selected, lower ones are not, and only the bucket's own
 // keys (a few hundred of 16384 in the benchmark's layers) are read as 64-bit
-// scores, at most kTopkOwn a thread, and searched by radix, 11 bits at a time
-// from the first bit in which they differ.  A bucket too large for that is
-// searched in place.  Bound by its chain of barriers (one workgroup per head):
+// scores, from a list of them, and searched by radix, 11 bits at a time over
+// the bits in which they differ.  A bucket too large for the list (1024 keys, a
+// key a thread; 4096 beyond T = 32768) is searched in place: each thread's own
+// keys in registers up to T = 32768, beyond that consecutive keys by consecutive
+// threads, eight loads of a thread in flight, in every pass.
+// Such buckets are those of peaked scores (most keys below the digits' range)
+// or nearly equal ones: 4 heads, peaked votes of 16384 keys 81.6 us a selection
+// with every key read by itself in each pass, 29.4 so; masses within 1% of
+// 16384 / 32768 / 100000 keys 56 / 102 / 258 and 18.6 / 27.4 / 123.  A list
+// limit of 128 keys costs 4 to 10 us at 16384 and 32768 keys.
+// Bound by its chain of barriers (one workgroup per head):
 // with all 64-bit keys in registers and their top bits as the first digit it
 // took 15.4 us a call for 16 heads of 16384 keys, and in sweeps 75 us for 4 of
 // 40000; this form takes 9.0 and 11.0 (8.3 and 11.8 within a layer).
-constexpr int kTopkOwn = 4;
-constexpr uint32_t kTopkList = kTopkOwn * kSelThreads;
 constexpr int kTopkMaxKpt = 512;         // keys per thread (T = 524288) up to which selection bits fit in LDS
 // Bucket sizes up to here: every key ranked against all others (beyond, the
 // 64-bit comparisons cost more than radix passes: 4 us at 200 keys).
 constexpr uint32_t kTopkRank = 128;
+// MASS mode, bucket sizes up to here: the bits that all keys of the bucket
+// share are taken from its digit; beyond, where a pass over equal keys would
+// cost more than finding that they are, from the keys (4 heads, masses within
+// 1% / all equal: 12.8 / 21.0 us and 13.3 / 12.8 at 4096 keys, 17.5 / 43.4 and
+// 18.6 / 17.9 at 16384).
+constexpr uint32_t kTopkKnown = 4096;
 
 template <int KPT>
 __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
     static_assert(KPT % 8 == 0, "whole 16-byte pieces of digits");
     static_assert(KPT <= 32, "one word of selection bits a thread");
     constexpr int kWords = KPT > 0 ? 1 : kTopkMaxKpt / 32;   // words of selection bits per thread
+    constexpr int kOwn = KPT > 0 ? 1 : 4;                    // listed keys per thread
+    constexpr uint32_t kList = kOwn * kSelThreads;
     __shared__ uint32_t cnt[2][2048];                    // radix pass p counts into cnt[p % 2]
-    __shared__ int32_t list[kTopkList];                  // the bucket's keys (indices), in any order
+    __shared__ int32_t list[kList];                      // the bucket's keys (indices), in any order
     __shared__ uint32_t picked[kWords][kSelThreads];
     __shared__ uint32_t wtot[kSelWaves];
-    __shared__ unsigned long long s_diff, s_first;
+    __shared__ unsigned long long s_ones, s_zeros;
     __shared__ uint32_t same_bits[kWords];
     __shared__ uint32_t s_digit, s_cnt, s_rem, n_list;
 
@@ -495,14 +509,22 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
     };
 #pragma unroll
     for (int q = 0; q < KPT / 2; ++q) pk[q] = clip(pk[q], 2 * q);
-    // f(j, stored digit) for this thread's keys, ascending, from memory: the
-    // in-place search of a bucket of many equal or nearly equal scores
+    // f(j, stored digit, key) for this thread's keys, ascending, from memory,
+    // eight digits and keys fetched at once.  (Keys past the pool, up to seven,
+    // are whatever follows in the workspace; their digit is 0.)
+    const uint64_t* own_key = key + min(t0, static_cast<int64_t>(pool));
     auto each_mem = [&](auto&& f) {
 #pragma nounroll
-        for (int j0 = 0; j0 < own; j0 += 2) {
-            const uint32_t w = clip(*reinterpret_cast<const uint32_t*>(dig + j0), j0);
-            f(j0, w & 0xFFFFu);
-            f(j0 + 1, w >> 16);
+        for (int j0 = 0; j0 < own; j0 += 8) {
+            const u32x4 x = *reinterpret_cast<const u32x4*>(dig + j0);
+            uint64_t k[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) k[e] = own_key[j0 + e];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t w = clip(x[e / 2], j0 + (e & ~1));
+                f(j0 + e, (e & 1) ? w >> 16 : w & 0xFFFFu, k[e]);
+            }
         }
     };
 
@@ -521,7 +543,7 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
     };
     if (tid == 0) {
         n_list = 0;
-        s_diff = s_first = 0;
+        s_ones = s_zeros = 0;
         s_digit = 0xFFFFu;
         s_cnt = s_rem = 0;
     }
@@ -534,10 +556,11 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
         n_in = s_cnt;
         need = s_rem;
     }
-    const bool listed = (KPT > 0 || kpt <= kTopkMaxKpt) && n_in <= kTopkList;
+    const bool listed = (KPT > 0 || kpt <= kTopkMaxKpt) && n_in <= kList;
 
-    // the keys above the bucket as bits, and the bucket's list
-    uint32_t n_sel = 0;
+    // the keys above the bucket as bits, and the bucket's keys as bits (KPT >
+    // 0) and as a list: each wave takes its place in it with one atomic a word
+    uint32_t n_sel = 0, in_bits = 0;
     {
         uint32_t above = 0;
         auto eight = [&](int j0, const u32x4& x) {       // digits j0 .. j0 + 7
@@ -549,26 +572,36 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
                 eq |= (d == dg ? 1u : 0u) << e;
             }
             above |= gt << (j0 & 31);
+            in_bits |= eq << (j0 & 31);
             n_sel += static_cast<uint32_t>(__popc(gt));
-            if (listed) {
-                for (; eq != 0; eq &= eq - 1)
-                    list[atomicAdd(&n_list, 1u)] = static_cast<int32_t>(t0) + j0 + __ffs(static_cast<int>(eq)) - 1;
-            }
+        };
+        auto word_done = [&](int w) {                    // the whole wave
+            picked[w][tid] = above;
+            if (__ballot(in_bits != 0u) == 0) return;
+            const uint32_t n = static_cast<uint32_t>(__popc(in_bits)), incl = wave_incl_scan(n);
+            uint32_t base = 0;
+            if (lane_id() == kWave - 1) base = atomicAdd(&n_list, incl);
+            base = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(base), kWave - 1));
+            uint32_t at = base + incl - n;
+            for (uint32_t m = in_bits; m != 0; m &= m - 1, ++at)
+                if (at < kList) list[at] = static_cast<int32_t>(t0) + 32 * w + __ffs(static_cast<int>(m)) - 1;
         };
         if constexpr (KPT > 0) {
 #pragma unroll
             for (int q = 0; q < KPT / 8; ++q) eight(8 * q, u32x4{pk[4 * q], pk[4 * q + 1], pk[4 * q + 2], pk[4 * q + 3]});
-            picked[0][tid] = above;
+            if (listed) word_done(0);
+            else picked[0][tid] = above;
         } else {
+            const int lim = __ballot(own > 0) != 0 ? kpt : 0;    // (whole waves)
 #pragma unroll 2
-            for (int j0 = 0; j0 < own; j0 += 8) {
+            for (int j0 = 0; j0 < lim; j0 += 8) {
                 u32x4 x = *reinterpret_cast<const u32x4*>(dig + j0);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) x[e] = clip(x[e], j0 + 2 * e);
                 eight(j0, x);
-                if (listed && ((j0 & 31) == 24 || j0 + 8 >= own)) {
-                    picked[j0 / 32][tid] = above;
-                    above = 0;
+                if (listed && ((j0 & 31) == 24 || j0 + 8 >= lim)) {
+                    word_done(j0 / 32);
+                    above = in_bits = 0;
                 }
             }
         }
@@ -597,26 +630,49 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
         }
         n_in = need = 0;                                 // nothing left to search
     }
-    // the bucket's keys of this thread's share of the list
-    uint64_t ck[kTopkOwn];
-    int32_t ct[kTopkOwn];
+    // the bucket's keys of this thread's share of the list, or, of a bucket too
+    // large for it, its own ones (all of its keys up to T = 32768)
+    uint64_t ck[kOwn];
+    int32_t ct[kOwn];
 #pragma unroll
-    for (int i = 0; i < kTopkOwn; ++i) {
+    for (int i = 0; i < kOwn; ++i) {
         const uint32_t at = static_cast<uint32_t>(tid + i * kSelThreads);
         const bool in = listed && at < min(n_in, n_list);
         ct[i] = in ? list[at] : -1;
         ck[i] = in ? key[ct[i]] : 0ull;
     }
-    // f(key) for the bucket's keys: this thread's share of the list, or its own
+    uint64_t kv[KPT > 0 ? KPT : 1];
+    if (!listed) {
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) kv[j] = own_key[j];
+    }
+    // f(key) for those
     auto in_bucket = [&](auto&& f) {
         if (listed) {
 #pragma unroll
-            for (int i = 0; i < kTopkOwn; ++i)
+            for (int i = 0; i < kOwn; ++i)
                 if (ct[i] >= 0) f(ck[i]);
+        } else if constexpr (KPT > 0) {
+#pragma unroll
+            for (int j = 0; j < KPT; ++j)
+                if ((in_bits >> j) & 1u) f(kv[j]);
         } else {
-            each_mem([&](int j, uint32_t d) {
-                if (d == dg) f(key[t0 + j]);
-            });
+            // (in any order: consecutive keys to consecutive threads)
+            const uint16_t* all = a.digits + hc * a.digit_stride;
+#pragma nounroll
+            for (int64_t t1 = tid; t1 < pool; t1 += 8 * kSelThreads) {
+                uint32_t d[8];
+                uint64_t k[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int64_t t = min(t1 + e * kSelThreads, static_cast<int64_t>(pool) - 1);
+                    d[e] = all[t];
+                    k[e] = key[t];
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (d[e] == dg && t1 + e * kSelThreads < pool) f(k[e]);
+            }
         }
     };
     // threshold: {key > theta} plus the first k_eq keys (by index) equal to
@@ -626,24 +682,40 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
     uint64_t theta = 0;
     uint32_t k_eq = 0;
     if (!whole) {
-        in_bucket([&](uint64_t kv) { s_first = kv; });   // any one of them
-        __syncthreads();
-        const uint64_t first = s_first;
-        uint64_t diff = 0;
-        in_bucket([&](uint64_t kv) { diff |= kv ^ first; });
+        // the bits in which they differ: set in one and clear in another
         // (reduced within the wave first: the compiler turns a per-lane atomic
         // of varying values into a loop over the lanes)
-        diff = wave_or_u64(diff);
-        if (lane_id() == 0 && diff != 0) atomicOr(&s_diff, static_cast<unsigned long long>(diff));
-        __syncthreads();
-        diff = s_diff;
+        uint64_t ones = 0, diff = 0;
+        if (a.mode != 0 && dg > 1u && dg < 2048u && n_in <= kTopkKnown) {
+            // a float mass between the two end digits: the digit is its
+            // exponent and upper 5 fraction bits, and the double's lower 29
+            // are zero (any value with these bits will do)
+            const uint32_t f = (dg - 1u + ((127u - 39u) << 5)) << 18;
+            ones = static_cast<uint64_t>(__double_as_longlong(static_cast<double>(__uint_as_float(f))));
+            diff = ((1ull << 18) - 1ull) << 29;
+        } else {
+            uint64_t zeros = 0;
+            in_bucket([&](uint64_t k) {
+                ones |= k;
+                zeros |= ~k;
+            });
+            ones = wave_or_u64(ones);
+            zeros = wave_or_u64(zeros);
+            if (lane_id() == 0) {
+                atomicOr(&s_ones, static_cast<unsigned long long>(ones));
+                atomicOr(&s_zeros, static_cast<unsigned long long>(zeros));
+            }
+            __syncthreads();
+            ones = s_ones;
+            diff = ones & s_zeros;
+        }
         if (diff == 0) {                                 // all equal: the first `need` by index
-            theta = first;
+            theta = ones;
             k_eq = need;
         } else {
-            const int top = 63 - __clzll(static_cast<long long>(diff));
+            const int top = 63 - __clzll(static_cast<long long>(diff)), low = __ffsll(static_cast<long long>(diff)) - 1;
             uint64_t mask = top == 63 ? 0ull : ~0ull << (top + 1);
-            uint64_t prefix = first & mask;
+            uint64_t prefix = ones & mask;
             int shift = max(top - 10, 0);
             for (int pass = 0;; ++pass) {
                 uint32_t* pc = cnt[pass & 1];
@@ -663,8 +735,8 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
                     theta = prefix - 1;
                     break;
                 }
-                if (shift == 0) {
-                    theta = prefix;
+                if (shift <= low) {                      // every bit below is the same in all of them
+                    theta = prefix | (ones & ((1ull << shift) - 1ull));
                     k_eq = need;
                     break;
                 }
@@ -676,9 +748,9 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
     uint32_t sel_total, pos;
     if (listed) {
         // the selected ones of the list, as bits of their owners
-        bool take[kTopkOwn];
+        bool take[kOwn];
 #pragma unroll
-        for (int i = 0; i < kTopkOwn; ++i) take[i] = ct[i] >= 0 && (whole || ck[i] > theta);
+        for (int i = 0; i < kOwn; ++i) take[i] = ct[i] >= 0 && (whole || ck[i] > theta);
         if (k_eq > 0) {
             // equal keys by index, in time that does not grow with their
             // number: counted per owner (the count buffers are all zero after
@@ -688,7 +760,7 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
             uint32_t *same = cnt[0], *taken = cnt[1];
             __syncthreads();
 #pragma unroll
-            for (int i = 0; i < kTopkOwn; ++i)
+            for (int i = 0; i < kOwn; ++i)
                 if (ct[i] >= 0 && ck[i] == theta) atomicAdd(&same[owner_of(ct[i])], 1u);
             if (tid < kWords) same_bits[tid] = 0;
             __syncthreads();
@@ -697,7 +769,7 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
             taken[tid] = before < k_eq ? min(mine, k_eq - before) : 0u;
             __syncthreads();
 #pragma unroll
-            for (int i = 0; i < kTopkOwn; ++i) {
+            for (int i = 0; i < kOwn; ++i) {
                 if (ct[i] < 0 || ck[i] != theta) continue;
                 const int o = owner_of(ct[i]), j = ct[i] - o * kpt;
                 take[i] = taken[o] == same[o];
@@ -705,7 +777,7 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
             }
             __syncthreads();
 #pragma unroll
-            for (int i = 0; i < kTopkOwn; ++i) {
+            for (int i = 0; i < kOwn; ++i) {
                 if (ct[i] < 0 || ck[i] != theta) continue;
                 const int o = owner_of(ct[i]), j = ct[i] - o * kpt;
                 if (taken[o] == 0 || taken[o] == same[o]) continue;
@@ -715,9 +787,27 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
             }
         }
 #pragma unroll
-        for (int i = 0; i < kTopkOwn; ++i)
+        for (int i = 0; i < kOwn; ++i)
             if (take[i]) pick(ct[i]);
         __syncthreads();
+    } else if constexpr (KPT > 0) {
+        uint32_t gt = 0, eq = 0;
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) {
+            gt |= (whole || kv[j] > theta ? 1u : 0u) << j;
+            eq |= (kv[j] == theta ? 1u : 0u) << j;
+        }
+        if (k_eq > 0) {
+            // the first k_eq equal keys by index
+            eq &= in_bits;
+            uint32_t eq_total;
+            const uint32_t n_eq = static_cast<uint32_t>(__popc(eq));
+            const uint32_t before = block_excl_scan<uint32_t>(n_eq, wtot, eq_total);
+            for (uint32_t n = before < k_eq ? min(n_eq, k_eq - before) : 0u; n > 0; --n, eq &= eq - 1) gt |= eq & (0u - eq);
+        }
+        picked[0][tid] |= gt & in_bits;
+    }
+    if (KPT > 0 || listed) {
         n_sel = 0;
         for (int w = 0; w < n_words; ++w) n_sel += static_cast<uint32_t>(__popc(picked[w][tid]));
         pos = block_excl_scan<uint32_t>(n_sel, wtot, sel_total);
@@ -729,11 +819,10 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
         }
     } else {
         uint32_t n_eq = 0;
-        each_mem([&](int j, uint32_t d) {
+        each_mem([&](int, uint32_t d, uint64_t k) {
             if (d != dg) return;
-            const uint64_t kv = key[t0 + j];
-            n_sel += whole || kv > theta ? 1u : 0u;
-            n_eq += kv == theta ? 1u : 0u;
+            n_sel += whole || k > theta ? 1u : 0u;
+            n_eq += k == theta ? 1u : 0u;
         });
         if (k_eq > 0) {
             // this thread's share of the k_eq equal keys, by index
@@ -744,12 +833,11 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
         }
         pos = block_excl_scan<uint32_t>(n_sel, wtot, sel_total);
         if (n_sel > 0) {
-            each_mem([&](int j, uint32_t d) {
+            each_mem([&](int j, uint32_t d, uint64_t k) {
                 bool take = d > dg;
                 if (d == dg) {
-                    const uint64_t kv = key[t0 + j];
-                    take = whole || kv > theta;
-                    if (kv == theta && k_eq > 0) {
+                    take = whole || k > theta;
+                    if (k == theta && k_eq > 0) {
                         take = true;
                         --k_eq;
                     }

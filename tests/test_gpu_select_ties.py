@@ -1,5 +1,6 @@
 """The top-k on scores at the limits of its first-digit buckets, against numpy:
-scores of every sign, and thousands of scores tied at the cut."""
+scores of every sign, thousands of scores tied at the cut, and buckets of nearly
+all keys."""
 import numpy as np
 import pytest
 import torch
@@ -82,3 +83,26 @@ def test_votes_alone(T, G, budget):
             votes[order[:int(np.searchsorted(run, 0.75 * run[-1])) + 1]] += 1
         want = np.append(_best(votes[:-1], budget - 1), T - 1)
         assert counts[0, c] == budget and np.array_equal(idx[0, c], want)
+
+
+@pytest.mark.parametrize("T,budget", [(129, 64), (1000, 256), (1025, 300), (4097, 409), (8193, 512), (16384, 8000),
+                                      (32768, 256), (32769, 256), (70001, 1024), (524289, 700)])
+@pytest.mark.parametrize("kind", ["near", "peaked", "tiny"])
+def test_large_buckets(T, budget, kind):
+    """Masses within 1%, masses over hundreds of octaves, and masses below the digits' range."""
+    import paper_2607_22586_amd as mm
+    print("buckets", T, budget, kind, flush=True)
+    rng = np.random.default_rng(T)
+    x = rng.standard_normal((1, 2, T))
+    mass = {"near": 0.3 * (1 + 0.01 * x), "peaked": np.exp2(-30 * np.abs(x)), "tiny": 2.0 ** -60 * np.exp2(x)}[kind]
+    mass = mass.astype(np.float32)
+    idx, counts = _select(mm.SelectionConfig(mode=mm.MMSKV_MASS, keep_last=False), budget, mass)
+    # the same as votes: one group whose tau-set is its largest mass, ranked by the anchor
+    gm = np.zeros((1, 2, 1, T), np.float32)
+    gm[..., T // 3] = 1.0
+    cfg = mm.SelectionConfig(P=32, G=1, keep_last=False)
+    vidx, vcounts = _select(cfg, budget, gm.sum(2), gm, mass)
+    for c in range(2):
+        assert counts[0, c] == budget and np.array_equal(idx[0, c], _best(mass[0, c], budget))
+        score = mass[0, c].astype(np.float64) + gm[0, c, 0]
+        assert vcounts[0, c] == budget and np.array_equal(vidx[0, c], _best(score, budget))
