@@ -169,7 +169,8 @@ int mmshiftkv_score_noalloc(const mmskv_shape *shape, const mmskv_params *params
 /* The two passes of mmshiftkv_score as separate calls (same arguments and
  * workspace), for callers that schedule or time them separately:
  * mmshiftkv_score_lse writes each row's log-sum-exp into the workspace;
- * mmshiftkv_score_mass then reads it and writes the outputs. */
+ * mmshiftkv_score_mass then reads it and writes the outputs (it leaves what
+ * the other calls wrote to the workspace as it is). */
 int mmshiftkv_score_lse(const mmskv_shape *shape, const mmskv_params *params,
                         const uint16_t *proxies, const uint16_t *q_last,
                         const void *k, int32_t k_dtype, const mmskv_strides *k_strides,

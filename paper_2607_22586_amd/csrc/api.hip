@@ -88,7 +88,7 @@ int status_of(hipError_t e) { return e == hipSuccess ? MMSKV_OK : MMSKV_EHIP; }
 struct ScoreLayout {
     ScorePlan plan;
     int n_kb, block_keys, mass_n_kb, rows, rows_pad, mass_unit;
-    size_t part_bytes, lse_off, total;
+    size_t part_bytes, lse_off, mass_off, total;
 };
 
 ScoreLayout score_layout(const mmskv_shape* s, const mmskv_params* p) {
@@ -109,7 +109,8 @@ ScoreLayout score_layout(const mmskv_shape* s, const mmskv_params* p) {
     const size_t heads = static_cast<size_t>(s->B) * s->Hkv;
     l.part_bytes = heads * l.n_kb * l.rows_pad * sizeof(float2);
     l.lse_off = align_up(l.part_bytes);
-    l.total = l.lse_off + align_up(heads * l.rows_pad * sizeof(float));
+    l.mass_off = l.lse_off + align_up(heads * l.rows_pad * sizeof(float));
+    l.total = l.mass_off + mass_part_bytes(heads, s->T, l.plan.mass_parts);
     return l;
 }
 
@@ -177,8 +178,8 @@ int prepare_score(const mmskv_shape* shape, const mmskv_params* params, const ui
     a->anchor_scale = query_scale(shape->d);
     a->lane_sum_hi = lane_sum_limit(shape->T, 16);     // pass 1 sums 16 keys per lane and chain
     a->part = static_cast<float2*>(ws);
-    a->mass_part = static_cast<float*>(ws);
     a->lse = reinterpret_cast<float*>(static_cast<char*>(ws) + l.lse_off);
+    a->mass_part = reinterpret_cast<float*>(static_cast<char*>(ws) + l.mass_off);
     a->group_mass = nullptr;
     a->mass = nullptr;
     a->anchor = nullptr;

@@ -20,6 +20,10 @@ struct ScorePlan {
     int lse_waves, lse_sub, mass_waves, lse_parts, mass_parts;
 };
 ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units, int mass_unit);
+// Workspace bytes of the row parts' partial masses.
+inline size_t mass_part_bytes(size_t heads, int T, int parts) {
+    return parts > 1 ? (heads * static_cast<size_t>(T) * parts * sizeof(float) + 255) / 256 * 256 : 0;
+}
 
 struct ProxyArgs {
     const void* q;        // [B, Hq, W, d]
@@ -57,7 +61,7 @@ struct ScoreArgs {
     float* lse;                // [B, Hkv, rows_pad]        log2-domain
     float* group_mass;         // [B, Hkv, G, T] or null
     float* mass;               // [B, Hkv, T]
-    float* mass_part;          // [mass_parts, B, Hkv, T] when mass_parts > 1 (in part's memory, which pass 2 does not read)
+    float* mass_part;          // [mass_parts, B, Hkv, T] when mass_parts > 1
     float* anchor;             // [B, Hkv, T]
 };
 

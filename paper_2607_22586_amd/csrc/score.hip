@@ -1320,16 +1320,20 @@ ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units
             }
         }
     }
-    // the partial masses of pass 2's row parts take the place of pass 1's
-    // partials, which are merged by then: no more parts than fit there
-    const int lse_keys = 32 * p.lse_sub * p.lse_waves;
-    const long fit = static_cast<long>((T + lse_keys - 1) / lse_keys) * rows_pad * 2 / T;
+    // the partial masses of pass 2's row parts lie behind pass 1's results
+    // (which stay as they are: the merge can be run again after a mass pass):
+    // no more parts than leave the whole within that scratch memory, where
+    // one part is
+    const size_t used = lse_bytes(heads * ((T + 32 * p.lse_sub * p.lse_waves - 1) / (32 * p.lse_sub * p.lse_waves)));
+    auto fits = [&](int r) {
+        return used > kScratchBytes || used + mass_part_bytes(static_cast<size_t>(heads), T, r) <= kScratchBytes;
+    };
     for (int w = 8; w >= 4; w -= 4) {
         // 8-wave mass blocks hold 8 staged tiles (68 KiB at d = 128) next to
         // the row normalisers; many rows take 4-wave blocks, which stage 4
         if (w == 8 && static_cast<size_t>(rows_pad) * sizeof(float) > kMaxRowLds8) continue;
         const long n = heads * ((T + 64 * w - 1) / (64 * w));
-        for (int r = 1; r <= kMaxMassParts && r <= mass_units && (r == 1 || (r <= fit && n * (r - 1) < 8 * kPlanCus)); ++r) {
+        for (int r = 1; r <= kMaxMassParts && r <= mass_units && (r == 1 || (fits(r) && n * (r - 1) < 8 * kPlanCus)); ++r) {
             const int part_tiles = (mass_units + r - 1) / r * mass_unit * Gh;
             if (r > 1 && part_tiles < 4) break;
             const double t = plan_time(w == 8 ? kMass8 : kMass4, n * r, part_tiles) + (r > 1 ? kMassCombine : 0.0);

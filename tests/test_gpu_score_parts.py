@@ -63,3 +63,23 @@ def test_parts_and_ragged_blocks(B, Hq, Hkv, T, d, P, G, dtype):
         # to 1024 fp32 terms add 6e-5
         err = (got.double() - want).abs()
         assert bool((err <= 6e-4 * want + 1e-30).all()), float((err / (want + 1e-30)).max())
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T,d,P,G", [(1, 7, 1, 1024, 128, 512, 32), (1, 28, 4, 4095, 128, 512, 32),
+                                              (1, 4, 1, 700, 64, 512, 32)])
+def test_merge_again_after_a_mass_pass(B, Hq, Hkv, T, d, P, G):
+    """The mass pass leaves the other stages' results in the workspace: the
+    merge and a second mass pass after it give the first one's bits."""
+    import paper_2607_22586_amd as mm
+    from paper_2607_22586_amd import workloads as wl
+    print("merge again", B, Hq, Hkv, T, d, P, G, flush=True)
+    x = wl.custom_layer(B, Hq, Hkv, T, 8, d, "bf16", seed=T, device="cuda:0")
+    cfg = mm.SelectionConfig(P=P, G=G, gamma=3.0, seed=1)
+    prox, ql = mm.build_proxies(x["q_win"], cfg, T, Hkv)
+    ws = torch.empty(mm.score_workspace(B, Hq, Hkv, T, 8, d, cfg), dtype=torch.uint8, device="cuda:0")
+    mm.score_lse(prox, ql, x["k"], cfg, ws, 8)
+    first = mm.score_mass(prox, ql, x["k"], cfg, ws, 8)
+    mm.score_lse(prox, ql, x["k"], cfg, ws, 8, stage="merge")
+    again = mm.score_mass(prox, ql, x["k"], cfg, ws, 8)
+    for a, b in ((first.group_mass, again.group_mass), (first.mass, again.mass), (first.anchor, again.anchor)):
+        assert torch.equal(a, b)
