@@ -137,7 +137,8 @@ int mmshiftkv_build_proxies(const mmskv_shape *shape, const mmskv_params *params
  *   anchor     [B, Hkv, T]     mean over the Gh heads of softmax(q_last)
  * The logit matrix never reaches memory: the call runs a row log-sum-exp
  * pass and a mass pass over the keys.  Workspace: mmshiftkv_score_workspace
- * bytes (256-byte aligned pointer). */
+ * bytes (256-byte aligned pointer); they never fall as B or T grows, so a
+ * buffer for the largest B and T serves smaller ones. */
 size_t mmshiftkv_score_workspace(const mmskv_shape *shape, const mmskv_params *params);
 int mmshiftkv_score(const mmskv_shape *shape, const mmskv_params *params,
                     const uint16_t *proxies, const uint16_t *q_last,
@@ -159,7 +160,7 @@ int mmshiftkv_score(const mmskv_shape *shape, const mmskv_params *params,
  * stream are safe.  Nothing in the array needs clearing between calls (each
  * call writes every byte it reads first).  A problem whose workspace
  * (mmshiftkv_score_workspace) exceeds the array returns MMSKV_ESCRATCH with
- * nothing enqueued; the benchmark workloads need at most ~17 MiB. */
+ * nothing enqueued; the benchmark workloads need at most ~22 MiB. */
 #define MMSKV_NOALLOC_SCRATCH_BYTES ((size_t)32 << 20)
 int mmshiftkv_score_noalloc(const mmskv_shape *shape, const mmskv_params *params,
                             const uint16_t *proxies, const uint16_t *q_last,

@@ -88,7 +88,7 @@ int status_of(hipError_t e) { return e == hipSuccess ? MMSKV_OK : MMSKV_EHIP; }
 struct ScoreLayout {
     ScorePlan plan;
     int n_kb, block_keys, mass_n_kb, rows, rows_pad, mass_unit;
-    size_t part_bytes, lse_off, mass_off, total;
+    size_t part_bytes, lse_off, mass_off, used, total;
 };
 
 ScoreLayout score_layout(const mmskv_shape* s, const mmskv_params* p) {
@@ -110,7 +110,8 @@ ScoreLayout score_layout(const mmskv_shape* s, const mmskv_params* p) {
     l.part_bytes = heads * l.n_kb * l.rows_pad * sizeof(float2);
     l.lse_off = align_up(l.part_bytes);
     l.mass_off = l.lse_off + align_up(heads * l.rows_pad * sizeof(float));
-    l.total = l.mass_off + mass_part_bytes(heads, s->T, l.plan.mass_parts);
+    l.used = l.mass_off + mass_part_bytes(heads, s->T, l.plan.mass_parts);
+    l.total = score_workspace_bound(static_cast<long>(heads), s->T, l.rows_pad);
     return l;
 }
 
@@ -149,7 +150,7 @@ int prepare_score(const mmskv_shape* shape, const mmskv_params* params, const ui
     const ScoreLayout l = score_layout(shape, params);
     // the mass pass keeps one head's row normalisers (rows_pad floats) in LDS
     if (static_cast<size_t>(l.rows_pad) * sizeof(float) > kMaxRowLds) return MMSKV_EUNSUPPORTED;
-    if (ws == nullptr || !aligned(ws, kAlign) || ws_bytes < l.total) return MMSKV_EWORKSPACE;
+    if (ws == nullptr || !aligned(ws, kAlign) || ws_bytes < l.total || l.used > l.total) return MMSKV_EWORKSPACE;
     a->proxies = proxies;
     a->q_last = q_last;
     a->k = k;

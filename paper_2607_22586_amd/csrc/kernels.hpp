@@ -20,10 +20,18 @@ struct ScorePlan {
     int lse_waves, lse_sub, mass_waves, lse_parts, mass_parts;
 };
 ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units, int mass_unit);
-// Workspace bytes of the row parts' partial masses.
+// Workspace bytes of pass 1's partials and row normalisers over n (head, key
+// block) pairs, and of the row parts' partial masses.
+inline size_t lse_bytes(long heads, long n, int rows_pad) {
+    return (static_cast<size_t>(n) * rows_pad * sizeof(float2) + 255) / 256 * 256 +
+           (static_cast<size_t>(heads) * rows_pad * sizeof(float) + 255) / 256 * 256;
+}
 inline size_t mass_part_bytes(size_t heads, int T, int parts) {
     return parts > 1 ? (heads * static_cast<size_t>(T) * parts * sizeof(float) + 255) / 256 * 256 : 0;
 }
+// Workspace bytes that suffice for every plan of a problem and never fall as B
+// or T grows, so that a buffer for the largest problem serves the smaller ones.
+size_t score_workspace_bound(long heads, int T, int rows_pad);
 
 struct ProxyArgs {
     const void* q;        // [B, Hq, W, d]

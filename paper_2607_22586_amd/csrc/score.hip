@@ -1281,6 +1281,11 @@ constexpr BlockCost kLse8{9.0, 1.72, 0.0}, kLse4{7.0, 0.93, 0.58};
 constexpr BlockCost kMass8{5.5, 0.88, 0.0}, kMass4{5.5, 0.93, 0.53};
 constexpr double kMassCombine = 3.0;                 // mass_combine_kernel
 constexpr int kMaxLseParts = 16;
+// (with 4 rounds of workgroups, more parts no longer level the last)
+constexpr long kPartBlocks = 8 * kPlanCus;
+// 256-key blocks of pass 1 up to two per CU: beyond, 1024-key blocks are as
+// fast and take a quarter of the partials
+constexpr long kLse4Blocks = 2 * kPlanCus;
 
 }  // namespace
 
@@ -1301,16 +1306,12 @@ ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units
     // that goes with the number of key blocks: where only the 8-wave blocks
     // keep it within the scratch memory of the allocation-free entry point,
     // they are taken (both entry points run the same plan)
-    auto lse_bytes = [&](long n) {
-        return (static_cast<size_t>(n) * rows_pad * sizeof(float2) + 255) / 256 * 256 +
-               (static_cast<size_t>(heads) * rows_pad * sizeof(float) + 255) / 256 * 256;
-    };
+    const size_t least = lse_bytes(heads, heads * ((T + 1023) / 1024), rows_pad);
     for (int w = 8; w >= 4; w -= 4) {
         const int keys = w == 8 ? 1024 : 256;
         const long n = heads * ((T + keys - 1) / keys);
-        if (w == 4 && lse_bytes(n) > kScratchBytes && lse_bytes(heads * ((T + 1023) / 1024)) <= kScratchBytes) continue;
-        // (with 4 rounds of workgroups, more parts no longer level the last)
-        for (int r = 1; r <= kMaxLseParts && (r == 1 || (tiles / r >= 4 && n * (r - 1) < 8 * kPlanCus)); ++r) {
+        if (w == 4 && (n > kLse4Blocks || (lse_bytes(heads, n, rows_pad) > kScratchBytes && least <= kScratchBytes))) continue;
+        for (int r = 1; r <= kMaxLseParts && (r == 1 || (tiles / r >= 4 && n * (r - 1) < kPartBlocks)); ++r) {
             const double t = plan_time(w == 8 ? kLse8 : kLse4, n * r, (tiles + r - 1) / r);
             if (p.lse_waves == 0 || t < best) {
                 best = t;
@@ -1324,7 +1325,8 @@ ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units
     // (which stay as they are: the merge can be run again after a mass pass):
     // no more parts than leave the whole within that scratch memory, where
     // one part is
-    const size_t used = lse_bytes(heads * ((T + 32 * p.lse_sub * p.lse_waves - 1) / (32 * p.lse_sub * p.lse_waves)));
+    const int lse_keys = 32 * p.lse_sub * p.lse_waves;
+    const size_t used = lse_bytes(heads, heads * ((T + lse_keys - 1) / lse_keys), rows_pad);
     auto fits = [&](int r) {
         return used > kScratchBytes || used + mass_part_bytes(static_cast<size_t>(heads), T, r) <= kScratchBytes;
     };
@@ -1333,7 +1335,7 @@ ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units
         // the row normalisers; many rows take 4-wave blocks, which stage 4
         if (w == 8 && static_cast<size_t>(rows_pad) * sizeof(float) > kMaxRowLds8) continue;
         const long n = heads * ((T + 64 * w - 1) / (64 * w));
-        for (int r = 1; r <= kMaxMassParts && r <= mass_units && (r == 1 || (fits(r) && n * (r - 1) < 8 * kPlanCus)); ++r) {
+        for (int r = 1; r <= kMaxMassParts && r <= mass_units && (r == 1 || (fits(r) && n * (r - 1) < kPartBlocks)); ++r) {
             const int part_tiles = (mass_units + r - 1) / r * mass_unit * Gh;
             if (r > 1 && part_tiles < 4) break;
             const double t = plan_time(w == 8 ? kMass8 : kMass4, n * r, part_tiles) + (r > 1 ? kMassCombine : 0.0);
@@ -1345,6 +1347,21 @@ ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units
         }
     }
     return p;
+}
+
+size_t score_workspace_bound(long heads, int T, int rows_pad) {
+    const long n8 = heads * ((T + 1023) / 1024), n4 = heads * ((T + 255) / 256);
+    const size_t lse8 = lse_bytes(heads, n8, rows_pad);
+    const size_t lse = lse_bytes(heads, n8 > kLse4Blocks ? n8 : n4 < kLse4Blocks ? n4 : kLse4Blocks, rows_pad);
+    // r > 1 parts of x = heads * T keys in blocks of at most 512:
+    // x / 512 * (r - 1) < kPartBlocks, so 4 r x < 4 (512 kPartBlocks + x)
+    // bytes, and x < 512 kPartBlocks
+    const size_t x = static_cast<size_t>(heads) * T, most = 512 * static_cast<size_t>(kPartBlocks);
+    const size_t keys = x < most ? x : most;
+    const size_t split = 4 * (kMaxMassParts * keys < most + keys ? kMaxMassParts * keys : most + keys);
+    const size_t all = lse + (split + 255) / 256 * 256;
+    // (plans keep to the allocation-free scratch where the least of them does)
+    return lse8 <= kScratchBytes && all > kScratchBytes ? kScratchBytes : all;
 }
 
 hipError_t launch_score_lse(const ScoreArgs& a, int stages, hipStream_t s) {
