@@ -280,7 +280,8 @@ typedef struct {
  * then the eighths in order; var = (SS - S*mean) / (T - std_ddof), negative
  * values clamped to 0.
  *   stats [B, 2, D] fp64 out (mean row, then std row), contiguous
- * Workspace: mmshiftkv_hidden_stats_workspace bytes (256-byte aligned). */
+ * Workspace: mmshiftkv_hidden_stats_workspace bytes (256-byte aligned), which
+ * never fall as B, T or D grows. */
 size_t mmshiftkv_hidden_stats_workspace(const mmskv_hshape *shape);
 int mmshiftkv_hidden_stats(const mmskv_hshape *shape, int32_t std_ddof,
                            const void *hidden, int32_t dtype, int64_t sb, int64_t st,

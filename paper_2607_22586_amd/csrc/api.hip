@@ -201,9 +201,7 @@ int check_hshape(const mmskv_hshape* s) {
 }
 
 size_t hidden_stats_ws(const mmskv_hshape* s) {
-    const size_t chunk = static_cast<size_t>(hidden_chunk(s->B, s->T, s->D));
-    const size_t chunks = (static_cast<size_t>(s->T) + chunk - 1) / chunk;
-    return align_up(static_cast<size_t>(s->B) * chunks * s->D * sizeof(double2));
+    return align_up(hidden_partials_bound(s->B, s->T, s->D) * sizeof(double2));
 }
 
 }  // namespace

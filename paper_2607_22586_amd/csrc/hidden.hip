@@ -43,6 +43,7 @@ __device__ __forceinline__ float scaled(float v, double scale) {
 }
 constexpr int kStatVec = 8;                 // features per thread (one 16-byte bf16 load)
 constexpr int kStatFlight = 8;              // tokens per group of loads in flight
+constexpr int kStatWaves = 4 * kPlanCus;    // waves of the chunk sums below which chunks are halved
 
 // Running sums of one token's kStatVec features.  The square of a bf16 or fp32
 // value is exact in fp64, so the fused multiply-add rounds exactly like a
@@ -641,8 +642,18 @@ constexpr WideForm kWide[] = {{128, 224, 3, 104}, {128, 128, 3, 68}, {64, 128, 4
 int hidden_chunk(int B, int T, int D) {
     const int64_t waves = static_cast<int64_t>(B) * ((D + kStatThreads * kStatVec - 1) / (kStatThreads * kStatVec));
     int chunk = 256;
-    while (chunk > 32 && waves * ((T + chunk - 1) / chunk) < 4 * kPlanCus) chunk /= 2;
+    while (chunk > 32 && waves * ((T + chunk - 1) / chunk) < kStatWaves) chunk /= 2;
     return chunk;
+}
+
+// Chunks of 256 tokens, or at most twice as many as leave less than
+// kStatWaves waves (a halving doubles them), a wave being at most 512 features.
+size_t hidden_partials_bound(int B, int T, int D) {
+    const size_t BD = static_cast<size_t>(B) * D, t = static_cast<size_t>(T);
+    const size_t whole = BD * ((t + 255) / 256), most = BD * ((t + 31) / 32);
+    const size_t halved = 2 * static_cast<size_t>(kStatWaves) * kStatThreads * kStatVec;
+    const size_t few = most < halved ? most : halved;
+    return whole > few ? whole : few;
 }
 
 hipError_t launch_hidden_stats(const HiddenArgs& a, hipStream_t s) {

@@ -189,6 +189,8 @@ int select_kpt(int T);
 inline int64_t select_digit_stride(int T) { return static_cast<int64_t>(select_kpt(T)) * 1024; }
 hipError_t launch_gather(const GatherArgs& a, hipStream_t s);
 int hidden_chunk(int B, int T, int D);       // tokens per partial sum of the hidden statistics
+// Partial sums that suffice for its chunks and never fall as B, T or D grows.
+size_t hidden_partials_bound(int B, int T, int D);
 hipError_t launch_hidden_stats(const HiddenArgs& a, hipStream_t s);
 hipError_t launch_hidden_proxies(const HiddenArgs& a, hipStream_t s);
 hipError_t launch_project(const ProjectArgs& p, hipStream_t s);
