@@ -101,7 +101,7 @@ ScoreLayout score_layout(const mmskv_shape* s, const mmskv_params* p) {
     // groups) when g16 is odd and g16 / 2 (one group) otherwise
     const int g16 = p->P / p->G / 16;
     l.mass_unit = g16 % 2 ? g16 : g16 / 2;
-    l.plan = score_plan(s->B, s->Hkv, s->T, l.rows_pad, Gh, p->P / 32 / l.mass_unit, l.mass_unit);
+    l.plan = score_plan(s->B, s->Hkv, s->T, s->d, l.rows_pad, Gh, p->P / 32 / l.mass_unit, l.mass_unit);
     const int lse_keys = 32 * l.plan.lse_sub * l.plan.lse_waves;
     l.n_kb = (s->T + lse_keys - 1) / lse_keys;
     l.block_keys = 64 * l.plan.mass_waves;

@@ -19,7 +19,7 @@ constexpr int kPlanCus = 256;              // CUs of the chip
 struct ScorePlan {
     int lse_waves, lse_sub, mass_waves, lse_parts, mass_parts;
 };
-ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units, int mass_unit);
+ScorePlan score_plan(int B, int Hkv, int T, int d, int rows_pad, int Gh, int mass_units, int mass_unit);
 // Workspace bytes of pass 1's partials and row normalisers over n (head, key
 // block) pairs, and of the row parts' partial masses.
 inline size_t lse_bytes(long heads, long n, int rows_pad) {

@@ -1257,28 +1257,67 @@ float lane_sum_limit(int T, int keys_per_sum) {
 
 namespace {
 
-// Modelled time (us) of n workgroups of `tiles` row tiles each.  A CU holds
-// one 8-wave workgroup or two 4-wave ones; a 4-wave workgroup alone on its CU
-// is faster than two that share it.
+// Modelled time (us) of a launch of n workgroups of `tiles` row tiles each, at
+// d = 128 and 64: with the chip to itself, and what it takes of the chip when
+// other streams fill the idle CUs (four calls in flight, by the call).  A CU
+// holds one 8-wave workgroup or two 4-wave ones; a 4-wave workgroup alone on its
+// CU is faster than two that share it.
 struct BlockCost {
-    double start, tile;          // 8-wave workgroup, or two 4-wave ones on a CU
-    double tile_alone;           // 4-wave workgroup alone on its CU (0: 8-wave)
+    bool two;                    // 4-wave workgroups: two on a CU
+    double start, tile[2];       // alone: launch, first tiles and keys; 8-wave, or two 4-wave ones on a CU
+    double tile_alone[2];        // 4-wave workgroup alone on its CU
+    double busy_start, busy_tile[2];
+    double busy_least;           // launch and gaps of a small call
 };
-double plan_time(const BlockCost& c, long n, int tiles) {
-    const long slots = c.tile_alone > 0.0 ? 2 * kPlanCus : kPlanCus;
+struct PlanTime {
+    double alone, busy;
+};
+PlanTime plan_time(const BlockCost& c, int d, long n, int tiles, double then) {
+    const int i = d == 64;
+    const long slots = c.two ? 2 * kPlanCus : kPlanCus;
     const long full = n / slots, rest = n % slots;
-    const double round = c.start + c.tile * tiles;
-    double t = full * round;
-    if (rest > 0) t += (c.tile_alone > 0.0 && rest <= kPlanCus) ? c.start + c.tile_alone * tiles : round;
+    const double round = c.start + c.tile[i] * tiles;
+    PlanTime t{full * round + then, n * (c.busy_start + c.busy_tile[i] * tiles) / slots};
+    if (rest > 0) t.alone += c.two && rest <= kPlanCus ? c.start + c.tile_alone[i] * tiles : round;
+    if (t.busy < t.alone / 4) t.busy = t.alone / 4;
+    if (t.busy < c.busy_least) t.busy = c.busy_least;
+    t.busy += then / 3;
     return t;
 }
 
-// Measured at d = 128 (launches of 100 to 2000 workgroups, 4 to 113 tiles
-// each): a tile of 8-wave blocks of 128 keys per wave (pass 1) takes 1.72 us,
-// of two 4-wave blocks of 64 per wave 0.93 us, of one alone 0.58 us; the
-// start (launch, first tiles, keys) 7 to 9 us.  Pass 2 alike.
-constexpr BlockCost kLse8{9.0, 1.72, 0.0}, kLse4{7.0, 0.93, 0.58};
-constexpr BlockCost kMass8{5.5, 0.88, 0.0}, kMass4{5.5, 0.93, 0.53};
+// The best plan so far, launches without parts tried first: a plan costs its
+// time alone plus kBusyWeight times what it takes of the chip beyond the fastest
+// of those.
+constexpr double kBusyWeight = 2.0;
+struct PlanChoice {
+    double alone = 0.0, busy = 0.0, cost = 0.0;
+    bool take(const PlanTime& t, int parts) {
+        if (parts == 1) {
+            if (alone > 0.0 && t.alone >= alone) return false;
+            alone = t.alone;
+            busy = t.busy;
+            cost = t.alone;
+            return true;
+        }
+        const double c = t.alone + kBusyWeight * (t.busy > busy ? t.busy - busy : 0.0);
+        if (c >= cost) return false;
+        cost = c;
+        return true;
+    }
+};
+
+// From 770 launches of each pass, on one and on four streams (1 to 32 heads of
+// 1 to 8 query heads each, 512 to 32768 keys, 8 to 129 tiles shared by 1 to 16
+// workgroups).  Every part fetches the keys again and starts anew, so parts take
+// more of the chip than one workgroup for all rows, and other streams then wait
+// for it: 28 query and 4 KV heads of 8192 keys, us a call on one / four streams,
+// pass 1 with 1, 2, 4, 8 parts 67 / 28, 42 / 29, 35 / 30, 40 / 35; pass 2 65 / 28,
+// 43 / 29, 39 / 34, 47 / 37 (4 and 2 are taken).  By the time alone, pass 2 took 4,
+// and 32 heads of 1000 keys went from 15.9 to 23.9 us on four streams.
+constexpr BlockCost kLse8{false, 9.0, {1.72, 1.15}, {0.0, 0.0}, 10.5, {1.62, 1.20}, 5.0};
+constexpr BlockCost kLse4{true, 7.0, {0.95, 0.60}, {0.58, 0.46}, 3.5, {0.95, 0.58}, 5.0};
+constexpr BlockCost kMass8{false, 9.0, {0.86, 0.64}, {0.0, 0.0}, 8.5, {0.86, 0.64}, 6.0};
+constexpr BlockCost kMass4{true, 7.0, {0.93, 0.66}, {0.53, 0.46}, 7.0, {0.93, 0.66}, 6.0};
 constexpr double kMassCombine = 3.0;                 // mass_combine_kernel
 constexpr int kMaxLseParts = 16;
 // (with 4 rounds of workgroups, more parts no longer level the last)
@@ -1289,32 +1328,32 @@ constexpr long kLse4Blocks = 2 * kPlanCus;
 
 }  // namespace
 
-// Block sizes and row parts with the smallest modelled time.  Large problems
+// Block sizes and row parts with the smallest modelled cost.  Large problems
 // (every CU has a whole 8-wave block of keys) keep all rows in one workgroup;
 // below that, and where the last round of workgroups would leave most CUs
 // idle, several workgroups share a key block's rows.  One layer of 28 query
-// and 4 KV heads, P = 512, both passes with all rows in one workgroup and
-// with the parts chosen here: T = 1000 157 -> 31 us, 4096 131 -> 50, 8191
-// 166 -> 77, 20000 238 -> 153; at 4 x 16384 keys more parts cost 7% each
-// doubling, since every part fetches the keys again.
-ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units, int mass_unit) {
+// and 4 KV heads, P = 512, both passes and merges with all rows in one
+// workgroup and with the parts chosen here, us on one / four streams: T = 1000
+// 158 / 47 and 30 / 15, 4096 129 / 49 and 52 / 36, 8192 135 / 59 and 80 / 62,
+// 16384 155 / 114 and 118 / 109.
+ScorePlan score_plan(int B, int Hkv, int T, int d, int rows_pad, int Gh, int mass_units, int mass_unit) {
     const long heads = static_cast<long>(B) * Hkv;
     const int tiles = rows_pad / 32;
     ScorePlan p{};
-    double best = 0.0;
+    PlanChoice lse, mass;
     // pass 1's partials and row normalisers take a share of the workspace
     // that goes with the number of key blocks: where only the 8-wave blocks
     // keep it within the scratch memory of the allocation-free entry point,
     // they are taken (both entry points run the same plan)
     const size_t least = lse_bytes(heads, heads * ((T + 1023) / 1024), rows_pad);
-    for (int w = 8; w >= 4; w -= 4) {
-        const int keys = w == 8 ? 1024 : 256;
-        const long n = heads * ((T + keys - 1) / keys);
-        if (w == 4 && (n > kLse4Blocks || (lse_bytes(heads, n, rows_pad) > kScratchBytes && least <= kScratchBytes))) continue;
-        for (int r = 1; r <= kMaxLseParts && (r == 1 || (tiles / r >= 4 && n * (r - 1) < kPartBlocks)); ++r) {
-            const double t = plan_time(w == 8 ? kLse8 : kLse4, n * r, (tiles + r - 1) / r);
-            if (p.lse_waves == 0 || t < best) {
-                best = t;
+    for (int r = 1; r <= kMaxLseParts && (r == 1 || tiles / r >= 4); ++r) {
+        for (int w = 8; w >= 4; w -= 4) {
+            const int keys = w == 8 ? 1024 : 256;
+            const long n = heads * ((T + keys - 1) / keys);
+            if (n * (r - 1) >= kPartBlocks) continue;
+            if (w == 4 && (n > kLse4Blocks || (lse_bytes(heads, n, rows_pad) > kScratchBytes && least <= kScratchBytes)))
+                continue;
+            if (lse.take(plan_time(w == 8 ? kLse8 : kLse4, d, n * r, (tiles + r - 1) / r, 0.0), r)) {
                 p.lse_waves = w;
                 p.lse_sub = keys / w / 32;
                 p.lse_parts = r;
@@ -1330,17 +1369,16 @@ ScorePlan score_plan(int B, int Hkv, int T, int rows_pad, int Gh, int mass_units
     auto fits = [&](int r) {
         return used > kScratchBytes || used + mass_part_bytes(static_cast<size_t>(heads), T, r) <= kScratchBytes;
     };
-    for (int w = 8; w >= 4; w -= 4) {
-        // 8-wave mass blocks hold 8 staged tiles (68 KiB at d = 128) next to
-        // the row normalisers; many rows take 4-wave blocks, which stage 4
-        if (w == 8 && static_cast<size_t>(rows_pad) * sizeof(float) > kMaxRowLds8) continue;
-        const long n = heads * ((T + 64 * w - 1) / (64 * w));
-        for (int r = 1; r <= kMaxMassParts && r <= mass_units && (r == 1 || (fits(r) && n * (r - 1) < kPartBlocks)); ++r) {
-            const int part_tiles = (mass_units + r - 1) / r * mass_unit * Gh;
-            if (r > 1 && part_tiles < 4) break;
-            const double t = plan_time(w == 8 ? kMass8 : kMass4, n * r, part_tiles) + (r > 1 ? kMassCombine : 0.0);
-            if (p.mass_waves == 0 || t < best) {
-                best = t;
+    for (int r = 1; r <= kMaxMassParts && r <= mass_units; ++r) {
+        const int part_tiles = (mass_units + r - 1) / r * mass_unit * Gh;
+        if (r > 1 && (part_tiles < 4 || !fits(r))) break;
+        for (int w = 8; w >= 4; w -= 4) {
+            // 8-wave mass blocks hold 8 staged tiles (68 KiB at d = 128) next to
+            // the row normalisers; many rows take 4-wave blocks, which stage 4
+            if (w == 8 && static_cast<size_t>(rows_pad) * sizeof(float) > kMaxRowLds8) continue;
+            const long n = heads * ((T + 64 * w - 1) / (64 * w));
+            if (n * (r - 1) >= kPartBlocks) continue;
+            if (mass.take(plan_time(w == 8 ? kMass8 : kMass4, d, n * r, part_tiles, r > 1 ? kMassCombine : 0.0), r)) {
                 p.mass_waves = w;
                 p.mass_parts = r;
             }
