@@ -628,11 +628,15 @@ hipError_t launch_wide(const ProjectArgs& p, hipStream_t s) {
 // Tile sizes and the measured time of one k step of a round of workgroups
 // (one per CU), in units of 10 ns: the loads, their wait and the barrier do not
 // shrink with the tile, so a tile is only worth its size while the grid fills
-// the CUs.
+// the CUs.  The two stages of a 128 x 128 tile leave a CU room for two
+// workgroups, which wait at different times: slower while each has a CU to
+// itself, and the fastest form of a grid of more (pair: the time of a round
+// with two on each CU).
 struct WideForm {
-    int m, n, stages, cost;
+    int m, n, stages, cost, pair;
 };
-constexpr WideForm kWide[] = {{128, 224, 3, 104}, {128, 128, 3, 68}, {64, 128, 4, 44}, {64, 64, 3, 33}};
+constexpr WideForm kWide[] = {{128, 224, 3, 104, 0}, {128, 128, 3, 68, 0}, {64, 128, 4, 44, 0}, {64, 64, 3, 33, 0},
+                              {128, 128, 2, 85, 103}};
 
 }  // namespace
 
@@ -679,17 +683,23 @@ hipError_t launch_project(const ProjectArgs& p, hipStream_t s) {
     // 128 x 128 and (2048 x 3584) 128 x 224 tiles in two stages that these
     // replace against the choice made here, M x N with K = N: 512 x 3584 47 ->
     // 25, 1024 x 3584 49 -> 37, 512 x 2048 24 -> 10.6, 1024 x 2048 25.6 -> 14.9,
-    // 2048 x 2048 27.5 -> 22.5; 2048 x 3584 with rotary tables 68 -> 56, and
-    // within a layer, its weights coming from memory, 77 -> 59 (71 with two
-    // stages).
+    // 2048 x 2048 27.5 -> 22.5; 2048 x 3584 with rotary tables 68 -> 57.
+    // 128 x 128 tiles in two stages, two workgroups on a CU, against the best of
+    // the other forms, the weights from another buffer each time: 2048 x 3584
+    // 57.4 and 59.1, 4096 x 3584 112 and 117, 2048 x 4096 67 and 84, 2048 x 8192
+    // (K = N) 268 and 324, 1024 x 4096 (256 tiles, one a CU) 57 and 42.
     int best = -1;
     int64_t best_cost = 0;
     if (p.K % kWK == 0 && p.K <= (1 << 20)) {          // (lane offsets within 32 bits)
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 5; ++i) {
             const WideForm& f = kWide[i];
             if (p.M % f.m != 0 || p.N % f.n != 0 || p.K < f.stages * kWK) continue;
             const int64_t tiles = static_cast<int64_t>(p.M / f.m) * (p.N / f.n);
-            const int64_t cost = (tiles + kPlanCus - 1) / kPlanCus * f.cost;
+            int64_t cost = (tiles + kPlanCus - 1) / kPlanCus * f.cost;
+            if (f.pair > 0) {
+                const int64_t rest = tiles % (2 * kPlanCus);
+                cost = tiles / (2 * kPlanCus) * f.pair + (rest > kPlanCus ? f.pair : rest > 0 ? f.cost : 0);
+            }
             if (best < 0 || cost < best_cost) {
                 best = i;
                 best_cost = cost;
@@ -701,6 +711,7 @@ hipError_t launch_project(const ProjectArgs& p, hipStream_t s) {
         case 1: return launch_wide<4, 4, 3>(p, s);
         case 2: return launch_wide<2, 4, 4>(p, s);
         case 3: return launch_wide<2, 2, 3>(p, s);
+        case 4: return launch_wide<4, 4, 2>(p, s);
         default: break;
     }
     dim3 g((p.M + kBM - 1) / kBM, (p.N + kBN - 1) / kBN);

@@ -126,7 +126,7 @@ def test_hidden_proxies_bit_exact(B, P, D, gamma, layer):
 @pytest.mark.parametrize("B,P,D,Hq,d,rope", [
     (2, 64, 3584, 28, 128, False), (3, 40, 200, 3, 64, False), (1, 50, 136, 2, 128, True),
     (2, 33, 3584, 4, 64, True), (1, 1, 8, 1, 64, False),
-    # too few k steps of 64 for any full tile (2), and 3 and 5
+    # widths that no tile of 128 columns divides: 2 k steps of 64, 3 and 5
     (2, 128, 128, 7, 64, False), (1, 128, 192, 14, 64, False), (1, 256, 320, 7, 64, False),
     # the same with rotation
     (2, 128, 128, 7, 64, True), (1, 128, 192, 14, 64, True), (1, 256, 128, 7, 128, True),
@@ -138,7 +138,11 @@ def test_hidden_proxies_bit_exact(B, P, D, gamma, layer):
     # 64 x 128 tiles (4 stages): 3 x 88 = 264 tiles of 64 x 64, at 4, 5 and 6 steps
     (1, 192, 256, 88, 64, True), (1, 192, 320, 44, 128, False), (3, 64, 384, 44, 128, True),
     # 128 x 128 tiles (3 stages): 5 x 32 tiles, 320 of 64 x 128
-    (5, 128, 192, 32, 128, True), (1, 640, 256, 64, 64, False), (5, 128, 320, 32, 128, False)])
+    (5, 128, 192, 32, 128, True), (1, 640, 256, 64, 64, False), (5, 128, 320, 32, 128, False),
+    # 128 x 128 tiles in 2 stages: their least reduction, and a grid of two
+    # workgroups a CU (16 x 32 tiles) at 2 to 5 steps
+    (1, 128, 128, 2, 64, True), (3, 128, 128, 5, 128, False), (1, 2048, 128, 32, 128, False),
+    (1, 2048, 192, 32, 128, True), (2, 1024, 256, 64, 64, False), (4, 512, 320, 32, 128, True)])
 def test_projection_within_bound(B, P, D, Hq, d, rope):
     rng_in = wl.custom_hidden(B, P, D, Hq, d, seed=B * 1000 + P)
     hp = rng_in["hidden"]                        # any bf16 [B, P, D] serves as samples
