@@ -216,20 +216,24 @@ __device__ __forceinline__ uint32_t* plane_word(const SelectArgs& a, int64_t hc,
 constexpr int kSweepBatch = 8;
 
 // f(t, bits of m[t]) for every key t of a row, the same trip count on every
-// thread; t >= T (bits 0) marks a lane without a key.
+// thread; t >= T (bits 0) marks a lane without a key (t is unsigned).
 template <typename F>
 __device__ __forceinline__ void sweep_row(const uint32_t* m, int T, F f) {
-    for (int base = 0; base < T; base += kSelThreads * kSweepBatch) {
+    // (unsigned: a batch of steps of 1024 keys may pass 2^31 - 1 at the longest rows)
+    constexpr uint32_t kStep = kSelThreads * kSweepBatch;
+    static_assert(static_cast<uint64_t>(INT32_MAX) + 2 * kStep <= UINT32_MAX, "row indices of a batch");
+    const uint32_t n = static_cast<uint32_t>(T);
+    for (uint32_t base = 0; base < n; base += kStep) {
         uint32_t v[kSweepBatch];
 #pragma unroll
         for (int k = 0; k < kSweepBatch; ++k) {
-            const int t = base + k * kSelThreads + static_cast<int>(threadIdx.x);
-            v[k] = t < T ? m[t] : 0u;
+            const uint32_t t = base + k * kSelThreads + threadIdx.x;
+            v[k] = t < n ? m[t] : 0u;
         }
 #pragma unroll
         for (int k = 0; k < kSweepBatch; ++k) {
             // (uniform: whole waves past the row have nothing to do)
-            if (base + k * kSelThreads < T) f(base + k * kSelThreads + static_cast<int>(threadIdx.x), v[k]);
+            if (base + k * kSelThreads < n) f(base + k * kSelThreads + threadIdx.x, v[k]);
         }
     }
 }
@@ -249,6 +253,7 @@ __global__ void __launch_bounds__(kSelThreads) tau_cut_kernel(SelectArgs a) {
     const uint32_t* m = reinterpret_cast<const uint32_t*>(a.group_mass) + hcg * a.T;
     const int tid = threadIdx.x;
     const int S = a.fix_shift;
+    const uint32_t n = static_cast<uint32_t>(a.T);
     clear_hist0_share(a, hc, g);
 
     // every mass below the fixed-point resolution: empty set
@@ -261,8 +266,8 @@ __global__ void __launch_bounds__(kSelThreads) tau_cut_kernel(SelectArgs a) {
         const uint32_t mask = tau_mask(pass);
         for (int i = tid; i < 2048; i += kSelThreads) { cnt[i] = 0; sum[i] = 0; }
         __syncthreads();
-        sweep_row(m, a.T, [&](int t, uint32_t bits) {
-            if (t < a.T && (bits & mask) == prefix) {
+        sweep_row(m, a.T, [&](uint32_t t, uint32_t bits) {
+            if (t < n && (bits & mask) == prefix) {
                 const uint32_t dg = tau_digit(bits, pass);
                 atomicAdd(&cnt[dg], 1u);
                 atomicAdd(&sum[dg], static_cast<unsigned long long>(mant_part(bits, S)));
@@ -294,8 +299,8 @@ __global__ void __launch_bounds__(kSelThreads) tau_cut_kernel(SelectArgs a) {
         if (pass < 2 && s_cnt == 1u) {
             // one key left in the crossing bucket: its mass is theta
             const uint32_t fixed = tau_fixed(pass);
-            sweep_row(m, a.T, [&](int t, uint32_t bits) {
-                if (t < a.T && (bits & fixed) == prefix) s_theta = bits;
+            sweep_row(m, a.T, [&](uint32_t t, uint32_t bits) {
+                if (t < n && (bits & fixed) == prefix) s_theta = bits;
             });
             __syncthreads();
             prefix = s_theta;
@@ -333,10 +338,10 @@ __global__ void __launch_bounds__(kSelThreads) tau_cut_kernel(SelectArgs a) {
     }
     // membership plane: each wave's 64 consecutive keys are two words
     const int lane = lane_id();
-    sweep_row(m, a.T, [&](int t, uint32_t bits) {
-        const uint64_t mb = __ballot(t < a.T && in_tau_set(bits, t, theta, tcut));
-        const int w = (t & ~(kWave - 1)) / 32 + lane;
-        if (lane < 2 && 32 * w < a.T) *plane_word(a, hc, g, w) = static_cast<uint32_t>(mb >> (32 * lane));
+    sweep_row(m, a.T, [&](uint32_t t, uint32_t bits) {
+        const uint64_t mb = __ballot(t < n && in_tau_set(bits, static_cast<int>(t), theta, tcut));
+        const uint32_t w = t / kWave * (kWave / 32) + lane;
+        if (lane < 2 && 32 * w < n) *plane_word(a, hc, g, static_cast<int>(w)) = static_cast<uint32_t>(mb >> (32 * lane));
     });
 }
 
