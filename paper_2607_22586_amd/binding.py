@@ -165,9 +165,17 @@ def _strides4(t: torch.Tensor) -> Strides:
     return Strides(t.stride(0), t.stride(1), t.stride(2))
 
 
+def _public_stream(index: int) -> int:
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+# the raw handle, without a Stream object around it (not part of torch's public
+# interface: its public form where a version lacks it)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _public_stream)
+
+
 def _stream(device) -> int:
-    # the raw handle, without a Stream object around it
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    return _raw_stream(device.index)
 
 
 def _p(t):
@@ -175,7 +183,7 @@ def _p(t):
     return None if t is None else t.data_ptr()
 
 
-class _on:
+class _RawGuard:
     """The device of a tensor made current around a call, and put back."""
     __slots__ = ("index", "before")
 
@@ -188,6 +196,11 @@ class _on:
     def __exit__(self, *exc):
         torch.cuda._maybe_exchange_device(self.before)
         return False
+
+
+# (the same of the light form of torch.cuda.device)
+_on = (_RawGuard if hasattr(torch.cuda, "_exchange_device") and hasattr(torch.cuda, "_maybe_exchange_device")
+       else torch.cuda.device)
 
 
 def _tables(rope, dev):
