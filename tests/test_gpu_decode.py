@@ -99,14 +99,17 @@ def test_decode_check_fp32_cache():
 
 # B, Hq, Hkv, T, d, dtype, decode queries, budget: one key and one query; fewer
 # keys than a wave's 64; exactly one chunk of 256 kept keys and one more; 33 and
-# 256 rows of a KV head (a second row tile, the most); 65 and 129 key blocks
-# (a second and a third round of the coverage merge)
+# 256 rows of a KV head (a second row tile, the most); 65 and 129 key blocks (a
+# round of the coverage merge takes 32 at d = 64 and 64 at d = 128: a third and
+# a fifth round, a second and a third)
 @pytest.mark.parametrize("B,Hq,Hkv,T,d,dtype,n_dec,budget", [
     (1, 1, 1, 1, 64, "bf16", 1, 1), (2, 2, 1, 1, 128, "fp32", 1, 4), (1, 4, 2, 50, 128, "bf16", 3, 20),
     (1, 4, 2, 50, 64, "fp32", 3, 20), (2, 4, 2, 600, 128, "fp32", 4, 256), (1, 4, 2, 600, 128, "fp32", 4, 257),
     (1, 4, 2, 600, 64, "bf16", 4, 257), (1, 33, 1, 300, 128, "fp32", 1, 100), (1, 11, 1, 300, 64, "bf16", 3, 100),
     (1, 16, 1, 513, 128, "bf16", 16, 200), (1, 16, 1, 513, 64, "fp32", 16, 513),
-    (1, 2, 1, 65 * 256 - 3, 64, "bf16", 2, 40), (1, 2, 1, 128 * 256 + 1, 64, "fp32", 2, 40)])
+    (1, 2, 1, 65 * 256 - 3, 64, "bf16", 2, 40), (1, 2, 1, 128 * 256 + 1, 64, "fp32", 2, 40),
+    (1, 2, 1, 64 * 256 + 1, 128, "bf16", 2, 40), (1, 2, 1, 64 * 256 + 1, 128, "fp32", 2, 40),
+    (1, 2, 1, 128 * 256 + 1, 128, "bf16", 2, 40), (1, 2, 1, 128 * 256 + 1, 128, "fp32", 2, 40)])
 def test_decode_check_edges(B, Hq, Hkv, T, d, dtype, n_dec, budget):
     x = wl.custom_layer(B, Hq, Hkv, T, 4, d, dtype=dtype, seed=T + d)
     gen = torch.Generator().manual_seed(T)

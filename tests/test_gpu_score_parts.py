@@ -83,3 +83,26 @@ def test_merge_again_after_a_mass_pass(B, Hq, Hkv, T, d, P, G):
     again = mm.score_mass(prox, ql, x["k"], cfg, ws, 8)
     for a, b in ((first.group_mass, again.group_mass), (first.mass, again.mass), (first.anchor, again.anchor)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T,d,P,G,dtype", [
+    (1, 7, 1, 255, 128, 512, 32, "bf16"), (2, 28, 4, 1000, 128, 512, 32, "f32"), (1, 28, 4, 4095, 128, 512, 32, "bf16"),
+    (1, 32, 32, 777, 128, 512, 32, "bf16"), (1, 16, 2, 3000, 64, 64, 4, "f32"), (2, 8, 2, 12001, 64, 512, 32, "bf16")])
+def test_strides_do_not_change_the_bits(B, Hq, Hkv, T, d, P, G, dtype):
+    """Token-major and padded caches give the contiguous head-major result's
+    bits (which the test above holds to fp64)."""
+    import paper_2607_22586_amd as mm
+    from paper_2607_22586_amd import workloads as wl
+    print("strides", B, Hq, Hkv, T, d, P, G, dtype, flush=True)
+    x = wl.custom_layer(B, Hq, Hkv, T, 8, d, dtype, seed=T, device="cuda:0")
+    cfg = mm.SelectionConfig(P=P, G=G, gamma=3.0, seed=1)
+    prox, ql = mm.build_proxies(x["q_win"], cfg, T, Hkv)
+    k = x["k"]
+    want = mm.score(prox, ql, k, cfg, 8)
+    tokens = k.transpose(1, 2).contiguous().transpose(1, 2)
+    slack = torch.full((B, Hkv, T + 3, d + 16), float("nan"), dtype=k.dtype, device=k.device)
+    slack[:, :, :T, :d] = k
+    for view in (tokens, slack[:, :, :T, :d]):
+        got = mm.score(prox, ql, view, cfg, 8)
+        for a, b in ((want.group_mass, got.group_mass), (want.mass, got.mass), (want.anchor, got.anchor)):
+            assert torch.equal(a, b)
