@@ -86,14 +86,6 @@ __device__ __forceinline__ U wave_incl_scan(U x) {
     return x;
 }
 
-// Sum over the 64 lanes, the same in every lane.
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-    const uint64_t x = wave_incl_scan(v);
-    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(x)), 63));
-    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(x >> 32)), 63));
-    return (static_cast<uint64_t>(hi) << 32) | lo;
-}
-
 // Bitwise OR over the 64 lanes, the same in every lane.
 __device__ __forceinline__ uint64_t wave_or_u64(uint64_t x) {
     x |= dpp_take<0x111, 0xF>(x);

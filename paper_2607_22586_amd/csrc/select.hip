@@ -10,10 +10,10 @@
 //           (mass desc, index asc) prefix whose mass reaches tau * total.
 //           Masses are summed as integers in units of 2^-S (converted from
 //           the float bits exactly), so every decision is independent of
-//           summation order.  The register-resident variant (T <= 32768)
-//           stops its passes early once the crossing bucket holds one key;
-//           the sweep variant always runs all three.  Both end by writing
-//           the group's membership plane: one bit per key, 32 keys a word.
+//           summation order.  The register-resident variant (T <= 65536)
+//           and the sweep beyond stop their passes early once the crossing
+//           bucket holds one key, and end by writing the group's membership
+//           plane: one bit per key, 32 keys a word.
 // vote      vote = #groups whose set holds the key, counted from the planes'
 //           words; score = vote + lambda*anchor (fp64), or the total mass; and
 //           per head the counts of the scores' first digits for the top-k.
@@ -863,19 +863,14 @@ __global__ void __launch_bounds__(kSelThreads) topk_kernel(SelectArgs a) {
     if (tid == 0) a.counts[hc] = static_cast<int32_t>(written);
 }
 
-// ------------------------------------------- register-resident variants
-// For T <= 1024 * KPT the whole row of one workgroup fits in registers:
-// thread j holds elements [KPT*j, KPT*j + KPT) (index order), so the data
-// is read from memory once and every index-ordered step (ties, compaction)
-// needs one block scan instead of a sweep.
-
-// tau cut of one (b, c, group); same result as tau_cut_kernel.  NT threads
-// (512 up to T = 16384, so two workgroups share a CU and a launch of 512
-// workgroups is resident at once; 1024 up to T = 32768) of at most 128
-// VGPRs.  Thread i holds keys
-// 2048 q + 4 i + e (q < KPT / 4, e < 4), so every load is one contiguous
-// 16-byte piece per lane; the index-ordered steps (ties, the plane) go
-// through the 2048-key chunks q in order.
+// ------------------------------------------- register-resident tau cut
+// The tau cut of one (b, c, group) for T <= NT * KPT, where the row of one
+// workgroup fits in registers and is read from memory once; same result as
+// tau_cut_kernel.  NT threads (512 up to T = 16384, so two workgroups share a
+// CU and a launch of 512 workgroups is resident at once; 1024 up to T = 65536)
+// of at most 128 VGPRs.  Thread i holds keys 4 NT q + 4 i + e (q < KPT / 4, e <
+// 4), so every load is one contiguous 16-byte piece per lane; the index-ordered
+// steps (ties, the plane) go through the chunks q of 4 NT keys in order.
 template <int KPT, int NT>
 __global__ void __launch_bounds__(NT) tau_cut_reg_kernel(SelectArgs a) {
     static_assert(KPT % 4 == 0, "whole 4-key pieces per thread");
