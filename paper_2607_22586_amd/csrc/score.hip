@@ -1265,10 +1265,13 @@ namespace {
 struct BlockCost {
     bool two;                    // 4-wave workgroups: two on a CU
     double start, tile[2];       // alone: launch, first tiles and keys; 8-wave, or two 4-wave ones on a CU
-    double tile_alone[2];        // 4-wave workgroup alone on its CU
+    double start_alone, tile_alone[2];   // 4-wave workgroup alone on its CU
     double busy_start, busy_tile[2];
     double busy_least;           // launch and gaps of a small call
 };
+// Share of a full round that a call of few 4-wave workgroups takes on four
+// streams (measured with 32 to 128 workgroups at d = 128 and 64).
+constexpr double kShared[2] = {0.22, 0.27};
 struct PlanTime {
     double alone, busy;
 };
@@ -1277,18 +1280,22 @@ PlanTime plan_time(const BlockCost& c, int d, long n, int tiles, double then) {
     const long slots = c.two ? 2 * kPlanCus : kPlanCus;
     const long full = n / slots, rest = n % slots;
     const double round = c.start + c.tile[i] * tiles;
-    PlanTime t{full * round + then, n * (c.busy_start + c.busy_tile[i] * tiles) / slots};
-    if (rest > 0) t.alone += c.two && rest <= kPlanCus ? c.start + c.tile_alone[i] * tiles : round;
+    PlanTime t{full * round, n * (c.busy_start + c.busy_tile[i] * tiles) / slots};
+    if (rest > 0) t.alone += c.two && rest <= kPlanCus ? c.start_alone + c.tile_alone[i] * tiles : round;
+    // (four calls of few workgroups: as long as alone, and 4-wave ones share
+    // CUs although others are free)
     if (t.busy < t.alone / 4) t.busy = t.alone / 4;
-    if (t.busy < c.busy_least) t.busy = c.busy_least;
+    if (t.busy < kShared[i] * round) t.busy = kShared[i] * round;
     t.busy += then / 3;
+    if (t.busy < c.busy_least) t.busy = c.busy_least;
+    t.alone += then;
     return t;
 }
 
 // The best plan so far, launches without parts tried first: a plan costs its
-// time alone plus kBusyWeight times what it takes of the chip beyond the fastest
-// of those.
-constexpr double kBusyWeight = 2.0;
+// time alone, kBusyWeight times what it takes of the chip, and kExcessWeight
+// times what that is beyond the fastest of those.
+constexpr double kBusyWeight = 0.5, kExcessWeight = 2.0;
 struct PlanChoice {
     double alone = 0.0, busy = 0.0, cost = 0.0;
     bool take(const PlanTime& t, int parts) {
@@ -1296,10 +1303,10 @@ struct PlanChoice {
             if (alone > 0.0 && t.alone >= alone) return false;
             alone = t.alone;
             busy = t.busy;
-            cost = t.alone;
+            cost = t.alone + kBusyWeight * t.busy;
             return true;
         }
-        const double c = t.alone + kBusyWeight * (t.busy > busy ? t.busy - busy : 0.0);
+        const double c = t.alone + kBusyWeight * t.busy + kExcessWeight * (t.busy > busy ? t.busy - busy : 0.0);
         if (c >= cost) return false;
         cost = c;
         return true;
@@ -1314,10 +1321,10 @@ struct PlanChoice {
 // pass 1 with 1, 2, 4, 8 parts 67 / 28, 42 / 29, 35 / 30, 40 / 35; pass 2 65 / 28,
 // 43 / 29, 39 / 34, 47 / 37 (4 and 2 are taken).  By the time alone, pass 2 took 4,
 // and 32 heads of 1000 keys went from 15.9 to 23.9 us on four streams.
-constexpr BlockCost kLse8{false, 9.0, {1.72, 1.15}, {0.0, 0.0}, 10.5, {1.62, 1.20}, 5.0};
-constexpr BlockCost kLse4{true, 7.0, {0.95, 0.60}, {0.58, 0.46}, 3.5, {0.95, 0.58}, 5.0};
-constexpr BlockCost kMass8{false, 9.0, {0.86, 0.64}, {0.0, 0.0}, 8.5, {0.86, 0.64}, 6.0};
-constexpr BlockCost kMass4{true, 7.0, {0.93, 0.66}, {0.53, 0.46}, 7.0, {0.93, 0.66}, 6.0};
+constexpr BlockCost kLse8{false, 9.0, {1.72, 1.15}, 0.0, {0.0, 0.0}, 10.5, {1.62, 1.20}, 5.0};
+constexpr BlockCost kLse4{true, 7.5, {0.95, 0.62}, 6.5, {0.61, 0.46}, 3.5, {0.95, 0.60}, 5.0};
+constexpr BlockCost kMass8{false, 9.0, {0.86, 0.64}, 0.0, {0.0, 0.0}, 8.5, {0.86, 0.64}, 6.0};
+constexpr BlockCost kMass4{true, 10.0, {0.93, 0.66}, 7.5, {0.55, 0.46}, 7.0, {0.93, 0.66}, 6.0};
 constexpr double kMassCombine = 3.0;                 // mass_combine_kernel
 constexpr int kMaxLseParts = 16;
 // (with 4 rounds of workgroups, more parts no longer level the last)
@@ -1334,8 +1341,8 @@ constexpr long kLse4Blocks = 2 * kPlanCus;
 // idle, several workgroups share a key block's rows.  One layer of 28 query
 // and 4 KV heads, P = 512, both passes and merges with all rows in one
 // workgroup and with the parts chosen here, us on one / four streams: T = 1000
-// 158 / 47 and 30 / 15, 4096 129 / 49 and 52 / 36, 8192 135 / 59 and 80 / 62,
-// 16384 155 / 114 and 118 / 109.
+// 158 / 47 and 30 / 16, 4096 129 / 49 and 52 / 37, 8192 136 / 60 and 81 / 62,
+// 16384 153 / 118 and 119 / 112.
 ScorePlan score_plan(int B, int Hkv, int T, int d, int rows_pad, int Gh, int mass_units, int mass_unit) {
     const long heads = static_cast<long>(B) * Hkv;
     const int tiles = rows_pad / 32;
