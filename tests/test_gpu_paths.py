@@ -1,7 +1,7 @@
 """HIP paths that the workloads of the other parity tests do not reach (GPU),
 each against the CPU oracle through the C ABI with the bars of
 tests/parity.py:
-  * the sweep form of the tau cut (more than 16384 keys per group) at a
+  * the sweep form of the tau cut (more than 65536 keys per group) at a
     ragged key count, and the global-memory top-k (more than 32768 keys);
   * MASS mode on sampled heads of a full-size layer, in the benchmark's
     launch configuration;
@@ -62,11 +62,12 @@ def oracle_layer(x, cfg, budget):
 
 
 @pytest.mark.parametrize("T,Hq,budget,mode", [(20001, 4, 300, bd.MMSKV_VOTE), (32768, 2, 700, bd.MMSKV_VOTE),
-                                              (40000, 2, 500, bd.MMSKV_VOTE), (40000, 2, 123, bd.MMSKV_MASS)])
+                                              (40000, 2, 500, bd.MMSKV_VOTE), (40000, 2, 123, bd.MMSKV_MASS),
+                                              (70001, 2, 600, bd.MMSKV_VOTE)])
 def test_long_rows_sweep_paths(T, Hq, budget, mode):
-    """16384 < T <= 32768 takes the 1024-thread register tau cut (ragged at
-    T = 20001, full at 32768), T > 32768 the sweep tau cut and the global
-    top-k."""
+    """16384 < T <= 65536 takes the 1024-thread register tau cut (ragged at
+    T = 20001 and 40000, full at 32768), beyond that the sweep tau cut; T > 32768
+    the global top-k."""
     print("case long rows", T, Hq, budget, mode, flush=True)
     x = wl.custom_layer(1, Hq, 1, T, 8, 64, seed=T + budget)
     cfg = bd.SelectionConfig(P=64, G=4, seed=T, mode=mode)

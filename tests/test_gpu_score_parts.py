@@ -17,13 +17,17 @@ SIZES = [
     (1, 4, 1, 31, 64, 64, 2, "f32"),
     (1, 7, 1, 33, 128, 512, 32, "bf16"),
     (1, 7, 1, 255, 128, 512, 32, "bf16"),
-    (2, 2, 2, 257, 64, 96, 2, "bf16"),          # 48 per group: split units of two groups
+    (2, 2, 2, 257, 64, 96, 2, "bf16"),          # 48 per group
+    (1, 7, 1, 300, 128, 768, 16, "bf16"),       # 48 per group, split in units of two groups
     (1, 8, 1, 545, 128, 192, 4, "f32"),
-    (1, 7, 1, 1024, 128, 512, 32, "bf16"),      # full blocks, 16 parts
+    (1, 7, 1, 1024, 128, 512, 32, "bf16"),      # full blocks, 15 and 16 parts
     (1, 12, 2, 1027, 128, 512, 8, "bf16"),      # 64 per group
     (4, 32, 32, 300, 64, 64, 4, "bf16"),        # two tiles a head: hardly anything to split
-    (1, 28, 4, 4095, 128, 512, 32, "bf16"),     # 8-wave mass blocks with parts
-    (1, 28, 4, 5000, 128, 512, 32, "f32"),
+    (1, 28, 4, 4095, 128, 512, 32, "bf16"),     # 8 and 4 parts
+    (1, 28, 4, 5000, 128, 512, 32, "f32"),      # 8-wave mass blocks with parts
+    (1, 16, 2, 8000, 64, 512, 32, "bf16"),      # the same at d = 64
+    (1, 28, 4, 12000, 128, 512, 32, "bf16"),    # 8-wave blocks with parts and early phases in both passes
+    (1, 28, 4, 16001, 128, 512, 32, "bf16"),    # the same with a ragged last block
     (16, 28, 4, 4001, 128, 512, 32, "bf16"),    # 1024-key blocks, the last one ragged
     (16, 28, 4, 4064, 128, 64, 4, "bf16"),      # the same with a last sub-tile that is full
 ]
